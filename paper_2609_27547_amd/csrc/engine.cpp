@@ -489,9 +489,7 @@ struct BlockCall {
     const StackDims* sd = nullptr;
     const LayerW* w = nullptr;
     PagedKV kv;
-    const int* seq_env = nullptr;
-    const int* row_seq = nullptr;
-    const int* row_pos = nullptr;
+    const int2* row_dst = nullptr;   // position and cache block of each row
     bool use_rope = true;
     // attention
     bool decode = false;
@@ -522,9 +520,9 @@ int run_block(ebrl_policy* p, BlockCall& b) {
     // fused QKV projection: rotary embedding of Q and K and the paged K/V
     // write happen in the GEMM epilogue
     RopeKVArgs r;
-    r.bf16 = p->bf16; r.M = b.rows; r.q_heads = s.hq;
-    r.Q = p->Qb; r.ldq = qn; r.kv = b.kv; r.seq_env = b.seq_env; r.row_seq = b.row_seq;
-    r.row_pos = b.row_pos; r.cos_tab = p->cos_tab; r.sin_tab = p->sin_tab; r.use_rope = b.use_rope;
+    r.q_heads = s.hq;
+    r.Q = p->Qb; r.ldq = qn; r.kv = b.kv; r.row_dst = b.row_dst;
+    r.cos_tab = p->cos_tab; r.sin_tab = p->sin_tab; r.use_rope = b.use_rope;
     GemmArgs g;
     g.A = p->Xn; g.lda = s.d; g.B = b.w->qkv; g.ldb = s.d; g.M = b.rows; g.N = qkvn; g.K = s.d;
     g.epi = EPI_QKV; g.rope = &r; g.row_norm = fold;
@@ -585,6 +583,13 @@ int check_ids(ebrl_policy* p, const int32_t* ids, int n, bool need_prefix) {
             return fail(p, EBRL_E_STATE, "env %d has no prefix (call ebrl_prefill first)", e);
     }
     return EBRL_OK;
+}
+
+// Where position `pos` of env `env` lives: {position, physical block}, the
+// entry of a row_dst table.
+void add_row_dst(const ebrl_policy* p, std::vector<int>& dst, int env, int pos) {
+    dst.push_back(pos);
+    dst.push_back(p->bt_host[(size_t)env * p->bt_stride + pos / KV_BLOCK]);
 }
 
 PagedKV dec_kv(const ebrl_policy* p, int layer) {
@@ -649,19 +654,20 @@ int denoise(ebrl_policy* p, const int32_t* env_ids, int32_t n, const float* fnoi
     const bool seeded = !anoise || (F && !fnoise);
     const int rows = n * S, arows = n * c.chunk, frows = n * F;
     std::vector<int> seq_env(env_ids, env_ids + n), q_off(n), q_len(n, S), q_pos0(n), kv_len(n),
-        row_seq(rows), row_pos(rows), tseq, tq0, calls(n);
+        row_dst, tseq, tq0, calls(n);
+    row_dst.reserve((size_t)rows * 2);
     for (int i = 0; i < n; ++i) {
         const int T = p->envs[env_ids[i]].T;
         calls[i] = (int)p->envs[env_ids[i]].noise_calls;
         q_off[i] = i * S;
         q_pos0[i] = T;
         kv_len[i] = T + S;
-        for (int j = 0; j < S; ++j) { row_seq[i * S + j] = i; row_pos[i * S + j] = T + j; }
+        for (int j = 0; j < S; ++j) add_row_dst(p, row_dst, env_ids[i], T + j);
         for (int q0 = 0; q0 < S; q0 += ATTN_Q_TILE) { tseq.push_back(i); tq0.push_back(q0); }
     }
     Meta m;
     const size_t o_env = m.add(seq_env), o_off = m.add(q_off), o_len = m.add(q_len), o_pos0 = m.add(q_pos0),
-                 o_kvl = m.add(kv_len), o_rseq = m.add(row_seq), o_rpos = m.add(row_pos), o_tseq = m.add(tseq),
+                 o_kvl = m.add(kv_len), o_dst = m.add(row_dst), o_tseq = m.add(tseq),
                  o_tq0 = m.add(tq0), o_calls = m.add(calls);
     int* md = nullptr;
     if ((rc = upload_meta(p, m, false, &md))) return rc;
@@ -694,7 +700,7 @@ int denoise(ebrl_policy* p, const int32_t* env_ids, int32_t n, const float* fnoi
             for (int l = 0; l < c.exp_layers; ++l) {
                 BlockCall b;
                 b.R = p->X; b.rows = rows; b.sd = &p->exp; b.w = &p->L_exp[l]; b.kv = dec_kv(p, l);
-                b.seq_env = md + o_env; b.row_seq = md + o_rseq; b.row_pos = md + o_rpos;
+                b.row_dst = reinterpret_cast<const int2*>(md + o_dst);
                 b.pre.seq_env = md + o_env; b.pre.q_off = md + o_off; b.pre.q_len = md + o_len;
                 b.pre.q_pos0 = md + o_pos0; b.pre.kv_len = md + o_kvl; b.pre.tile_seq = md + o_tseq;
                 b.pre.tile_q0 = md + o_tq0; b.pre.n_tiles = (int)tseq.size(); b.pre.causal = false;
@@ -1149,9 +1155,10 @@ int ebrl_prefill(ebrl_policy* p, const ebrl_obs_batch* obs, const int32_t* env_i
     const int M = tok_off[n];
     if ((size_t)M > p->rows_cap) return fail(p, EBRL_E_INVALID, "internal: %d rows exceed capacity", M);
     for (int i = 0; i < n; ++i) last_row[i] = tok_off[i] + T[i] - 1;
-    std::vector<int> row_seq(M), row_pos(M);
+    std::vector<int> row_dst;
+    row_dst.reserve((size_t)M * 2);
     for (int i = 0; i < n; ++i)
-        for (int t = 0; t < T[i]; ++t) { row_seq[tok_off[i] + t] = i; row_pos[tok_off[i] + t] = t; }
+        for (int t = 0; t < T[i]; ++t) add_row_dst(p, row_dst, env_ids[i], t);
     std::vector<std::pair<int, int>> tiles;
     for (int i = 0; i < n; ++i)
         for (int q0 = 0; q0 < T[i]; q0 += ATTN_Q_TILE) tiles.push_back({i, q0});
@@ -1168,20 +1175,23 @@ int ebrl_prefill(ebrl_policy* p, const ebrl_obs_batch* obs, const int32_t* env_i
         }
     // ViT sequences
     const int pv = p->patches_per_env;
-    std::vector<int> v_ident(n), v_off(n), v_len(n, pv), v_zero(n, 0), v_rowseq, v_rowpos, v_tseq, v_tq0;
+    std::vector<int> v_ident(n), v_off(n), v_len(n, pv), v_zero(n, 0), v_dst, v_tseq, v_tq0;
     if (images && c.vit_layers) {
         for (int i = 0; i < n; ++i) { v_ident[i] = i; v_off[i] = i * pv; }
         for (int i = 0; i < n; ++i)
-            for (int t = 0; t < pv; ++t) { v_rowseq.push_back(i); v_rowpos.push_back(t); }
+            for (int t = 0; t < pv; ++t) {   // the ViT's scratch cache: identity block table
+                v_dst.push_back(t);
+                v_dst.push_back(i * p->vit_bt_stride + t / KV_BLOCK);
+            }
         for (int i = 0; i < n; ++i)
             for (int q0 = 0; q0 < pv; q0 += ATTN_Q_TILE) { v_tseq.push_back(i); v_tq0.push_back(q0); }
     }
     Meta m;
     const size_t o_env = m.add(seq_env), o_off = m.add(tok_off), o_len = m.add(T), o_pos0 = m.add(q_pos0),
-                 o_last = m.add(last_row), o_rseq = m.add(row_seq), o_rpos = m.add(row_pos),
+                 o_last = m.add(last_row), o_dst = m.add(row_dst),
                  o_tseq = m.add(tile_seq), o_tq0 = m.add(tile_q0), o_ldst = m.add(lang_dst),
                  o_lsrc = m.add(lang_src), o_vid = m.add(v_ident), o_voff = m.add(v_off), o_vlen = m.add(v_len),
-                 o_vzero = m.add(v_zero), o_vrseq = m.add(v_rowseq), o_vrpos = m.add(v_rowpos),
+                 o_vzero = m.add(v_zero), o_vdst = m.add(v_dst),
                  o_vtseq = m.add(v_tseq), o_vtq0 = m.add(v_tq0);
     int* md = nullptr;
     if ((rc = upload_meta(p, m, true, &md))) return rc;
@@ -1203,7 +1213,7 @@ int ebrl_prefill(ebrl_policy* p, const ebrl_obs_batch* obs, const int32_t* env_i
                 b.R = p->Vx; b.rows = n * pv; b.sd = &p->vit; b.w = &p->L_vit[l];
                 b.kv.base = p->vit_kv; b.kv.block_table = p->vit_bt; b.kv.bt_stride = p->vit_bt_stride;
                 b.kv.kv_heads = p->vit.hkv; b.kv.head_dim = p->vit.hd;
-                b.seq_env = md + o_vid; b.row_seq = md + o_vrseq; b.row_pos = md + o_vrpos; b.use_rope = false;
+                b.row_dst = reinterpret_cast<const int2*>(md + o_vdst); b.use_rope = false;
                 b.pre.seq_env = md + o_vid; b.pre.q_off = md + o_voff; b.pre.q_len = md + o_vlen;
                 b.pre.q_pos0 = md + o_vzero; b.pre.kv_len = md + o_vlen; b.pre.tile_seq = md + o_vtseq;
                 b.pre.tile_q0 = md + o_vtq0; b.pre.n_tiles = (int)v_tseq.size(); b.pre.causal = false;
@@ -1238,7 +1248,7 @@ int ebrl_prefill(ebrl_policy* p, const ebrl_obs_batch* obs, const int32_t* env_i
     for (int l = 0; l < c.layers; ++l) {
         BlockCall b;
         b.R = p->X; b.rows = M; b.sd = &p->dec; b.w = &p->L_dec[l]; b.kv = dec_kv(p, l);
-        b.seq_env = md + o_env; b.row_seq = md + o_rseq; b.row_pos = md + o_rpos;
+        b.row_dst = reinterpret_cast<const int2*>(md + o_dst);
         b.pre.seq_env = md + o_env; b.pre.q_off = md + o_off; b.pre.q_len = md + o_len; b.pre.q_pos0 = md + o_pos0;
         b.pre.kv_len = md + o_len; b.pre.tile_seq = md + o_tseq; b.pre.tile_q0 = md + o_tq0;
         b.pre.n_tiles = (int)tiles.size(); b.pre.causal = true; b.pre.max_kv_len = maxT;
@@ -1281,19 +1291,18 @@ int ebrl_decode_actions(ebrl_policy* p, const int32_t* env_ids, int32_t n, int32
     // split and reduction choice of the kernels depends on the problem shape
     // only, so the real rows' bits do not depend on the padding
     const int nc = n <= 4 ? n : std::min(p->dec_cap, (n + 7) / 8 * 8);
-    std::vector<int> seq_env(nc, p->pad_env), ident(nc);
+    std::vector<int> seq_env(nc, p->pad_env);
     std::copy(env_ids, env_ids + n, seq_env.begin());
-    std::iota(ident.begin(), ident.end(), 0);
-    std::vector<int> kvlen((size_t)std::max(steps, 1) * nc), pos((size_t)std::max(steps, 1) * nc);
-    for (int i = 0; i < nc; ++i) {
-        const int T = p->envs[seq_env[i]].T;
-        for (int k = 1; k <= steps; ++k) {
+    std::vector<int> kvlen((size_t)std::max(steps, 1) * nc), row_dst;
+    row_dst.reserve((size_t)std::max(steps, 1) * nc * 2);
+    for (int k = 1; k <= steps; ++k)
+        for (int i = 0; i < nc; ++i) {
+            const int T = p->envs[seq_env[i]].T;
             kvlen[(size_t)(k - 1) * nc + i] = T + k;
-            pos[(size_t)(k - 1) * nc + i] = T + k - 1;
+            add_row_dst(p, row_dst, seq_env[i], T + k - 1);
         }
-    }
     Meta m;
-    const size_t o_env = m.add(seq_env), o_id = m.add(ident), o_kvl = m.add(kvlen), o_pos = m.add(pos);
+    const size_t o_env = m.add(seq_env), o_kvl = m.add(kvlen), o_dst = m.add(row_dst);
     int* md = nullptr;
     if ((rc = upload_meta(p, m, false, &md))) return rc;
     // split count of the fp32 attention path: the policy's longest sequence
@@ -1320,7 +1329,7 @@ int ebrl_decode_actions(ebrl_policy* p, const int32_t* env_ids, int32_t n, int32
             for (int l = 0; l < c.layers; ++l) {
                 BlockCall b;
                 b.R = p->X; b.rows = nc; b.sd = &p->dec; b.w = &p->L_dec[l]; b.kv = dec_kv(p, l);
-                b.seq_env = md + o_env; b.row_seq = md + o_id; b.row_pos = md + o_pos + (size_t)(k - 1) * nc;
+                b.row_dst = reinterpret_cast<const int2*>(md + o_dst) + (size_t)(k - 1) * nc;
                 b.decode = true;
                 b.dec.seq_env = md + o_env; b.dec.kv_len = md + o_kvl + (size_t)(k - 1) * nc; b.dec.n = nc;
                 b.dec.max_splits = max_splits;

@@ -84,19 +84,12 @@ template <typename T> struct EpiSwiGLU {
 // Paired epilogue of the fused QKV projection: columns n (first half of a
 // head-local 32-row group) and n + 16 hold rotation partners e and e + hd/2.
 template <typename T> struct EpiQKV {
-    T* Q; int ldq; T* kv; const int* bt; int bt_stride; int hq, hkv, hd;
-    const int* seq_env; const int* row_seq; const int* row_pos;
+    T* Q; int ldq; T* kv; int hq, hkv, hd;
+    const int2* row_dst;
     const float* cos_tab; const float* sin_tab; int use_rope;
-    // Per-row part of the destination: the row's position and the element
-    // offset of its token row in head 0's K block (paged cache).
-    EBRL_DEV int4 row_info(int m) const {
-        const int pos = row_pos[m];
-        const int env = seq_env[row_seq[m]];
-        const int blk = bt[(size_t)env * bt_stride + (pos >> 4)];
-        const size_t off = (size_t)blk * 2 * hkv * KV_BLOCK * hd + (size_t)(pos & 15) * hd;
-        return make_int4(pos, (int)(uint32_t)off, (int)(uint32_t)(off >> 32), 0);
-    }
-    EBRL_DEV void pair_at(int4 ri, int m, int n, const float* x1, const float* x2) const {
+    // Per-row part of the destination: the row's position and its cache block.
+    EBRL_DEV int2 row_info(int m) const { return row_dst[m]; }
+    EBRL_DEV void pair_at(int2 ri, int m, int n, const float* x1, const float* x2) const {
         const int qn = hq * hd, kn = hkv * hd;
         const int region = n < qn ? 0 : (n < qn + kn ? 1 : 2);
         const int local = n - (region == 0 ? 0 : (region == 1 ? qn : qn + kn));
@@ -121,8 +114,9 @@ template <typename T> struct EpiQKV {
         if (region == 0) {
             dst = Q + (size_t)m * ldq + h * hd;
         } else {
-            const size_t off = (size_t)(uint32_t)ri.y | ((size_t)(uint32_t)ri.z << 32);
-            dst = kv + off + ((size_t)(region == 2 ? hkv : 0) + h) * KV_BLOCK * hd;
+            // token row pos % 16 of head h's K (or V) rows in the block
+            const size_t row = ((size_t)ri.y * 2 * hkv + (region == 2 ? hkv : 0) + h) * KV_BLOCK + (pos & (KV_BLOCK - 1));
+            dst = kv + row * hd;
         }
         st4<T>(dst + e, a[0], a[1], a[2], a[3]);
         st4<T>(dst + e + half, b[0], b[1], b[2], b[3]);
@@ -135,9 +129,8 @@ template <typename T> struct EpiQKV {
 template <class E> struct epi_row_info : std::false_type {};
 template <typename T> struct epi_row_info<EpiQKV<T>> : std::true_type {};
 template <typename T> EpiQKV<T> make_epi_qkv(const RopeKVArgs& r) {
-    return EpiQKV<T>{(T*)r.Q, r.ldq, (T*)r.kv.base, r.kv.block_table, r.kv.bt_stride, r.q_heads,
-                     r.kv.kv_heads, r.kv.head_dim, r.seq_env, r.row_seq, r.row_pos, r.cos_tab, r.sin_tab,
-                     (int)r.use_rope};
+    return EpiQKV<T>{(T*)r.Q, r.ldq, (T*)r.kv.base, r.q_heads, r.kv.kv_heads, r.kv.head_dim, r.row_dst,
+                     r.cos_tab, r.sin_tab, (int)r.use_rope};
 }
 
 // ------------------------------------------------------- bf16 MFMA GEMM --
@@ -289,26 +282,29 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(
 
 
 // ------------------------------------------------ bf16 MFMA GEMM, large M --
-// 256 x 256 macro tiles, 16 waves in 4 x 4 (64 x 64 per wave, four waves
-// per SIMD so that one wave's LDS waits overlap another's MFMAs); the
-// 192 x 256 and 128 x 128 variants run 12 waves of 64 x 64 and 8 of 64 x 32.
-// Operands go global -> LDS with global_load_lds_dwordx4 (no VGPR staging):
-// a wave instruction writes 64 lanes x 16 bytes contiguously, so the tile is
-// stored as 16-byte chunks, chunk (row, c) of a 64-element row at position
-// row * 8 + (c ^ (row & 7)); the XOR makes the MFMA fragment reads of 8
-// consecutive rows hit 8 different bank groups.  Two LDS stages: the loads of
-// K tile t+1 are in flight while tile t is multiplied.  Block ids are
-// remapped so that consecutive tiles of one row band run on the same XCD
-// (the dispatcher deals block ids round-robin over the 8 XCDs).
+// Operands go global -> LDS with global_load_lds_dwordx4 (no VGPR staging): a
+// wave instruction writes 64 lanes x 16 bytes contiguously, i.e. 8 rows of a
+// 64-wide K tile, stored as 16-byte chunks: chunk c of row q at q * 8 +
+// (c ^ (q & 7)); the XOR makes the MFMA fragment reads of 8 consecutive rows
+// hit 8 different bank groups.
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-EBRL_DEV void wait_vm_all() { __builtin_amdgcn_s_waitcnt(0); }
-
 // s_waitcnt on the vector-memory counter only (gfx9 encoding: expcnt and
-// lgkmcnt fields at their maxima).
+// lgkmcnt fields at their maxima), and on the LDS counter only.
 template <int N> EBRL_DEV void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt range");
     __builtin_amdgcn_s_waitcnt((N & 15) | 0x70 | 0xF00 | ((N >> 4) << 14));
+}
+EBRL_DEV void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+
+// Workgroup barrier without the waits of __syncthreads: the kernels below
+// count their own loads.  Neither memory accesses nor MFMAs move across it.
+EBRL_DEV void wg_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // global_load_lds_dwordx4 issued as inline assembly: the compiler neither
@@ -325,8 +321,6 @@ EBRL_DEV void dma16_to_lds_nt(const void* g, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
                  :: "v"(g), "s"(lds_addr) : "memory", "m0");
 }
-
-
 // The same DMA in its scalar-base form: a wave-uniform 64-bit base in SGPRs
 // plus a 32-bit per-lane byte offset, so a wave's row offsets stay fixed
 // across K tiles (only the scalar base advances) and take one VGPR each.
@@ -334,242 +328,442 @@ EBRL_DEV void dma16_to_lds_s(const void* sbase, uint32_t voff, uint32_t lds_addr
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(voff), "s"(sbase), "s"(lds_addr) : "memory", "m0");
 }
+// A wave-uniform address pinned to SGPRs (readfirstlane returns int: each half
+// goes through uint32_t, so the low half is zero-extended).
+EBRL_DEV const char* uniform_ptr(const void* p) {
+    const uint64_t b = (uint64_t)(uintptr_t)p;
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    return (const char*)(uintptr_t)(((uint64_t)hi << 32) | (uint64_t)lo);
+}
 
-// ROWS x 64 bf16 of G (rows row0_g.., columns k0..k0+63; rows past
-// rows_valid repeat the last valid row) into lds_tile, 16-byte chunk c of
-// row r at position r * 8 + (c ^ (r & 7)).  The loads go through inline
-// assembly: callers wait on vmcnt and synchronise before reading the tile.
-template <int ROWS, int NW>
-EBRL_DEV void load_tile_lds(const bf16_t* __restrict__ G, int ld, int row0_g, int rows_valid, int k0,
-                            bf16_t* lds_tile, int wave, int lane) {
-    // base and LDS addresses are wave-uniform: pinned to SGPRs (readfirstlane
-    // returns int: each half goes through uint32_t, so the low half is
-    // zero-extended)
-    const uint64_t b = (uint64_t)(uintptr_t)(G + (size_t)row0_g * ld + k0);
-    const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-    const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-    const void* const base = (const void*)(uintptr_t)(((uint64_t)b_hi << 32) | (uint64_t)b_lo);
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds_tile;
-    const int last = rows_valid - 1 - row0_g;
-    auto group = [&](int r0) {   // rows r0 .. r0+7, one instruction
-        const int row = r0 + (lane >> 3);
-        const int c = (lane & 7) ^ (row & 7);
-        const uint32_t voff = (uint32_t)(min(row, last) * ld + c * 8) * 2u;
-        dma16_to_lds_s(base, voff, __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)r0 * 128u));
-    };
-    if constexpr (ROWS % (8 * NW) == 0) {
-        // each of the NW waves fills ROWS/NW consecutive rows
+// Epilogue of one 16-row x COLS-column sub-tile that a wave has staged in LDS
+// (`at(row, chunk)`: its 16-byte chunk `chunk` of row `row`): read back
+// row-contiguous, so that each store (and the residual read) covers whole row
+// segments instead of 16-byte pieces of 16 rows.  INSIDE: no bounds checks;
+// a wave then issues exactly epi_stores<Epi> x COLS / 64 stores or more.
+// ri(row): row_info of a row (epilogues that use it).
+template <int COLS, bool PAIRED, bool INSIDE, class Epi, class At, class RowInfo>
+EBRL_DEV void store_subtile(const Epi& epi, int mrow0, int ncol0, int M, int N, int lane, At at, RowInfo ri) {
+    if constexpr (PAIRED) {
+        // COLS / 8 lanes per row: gate columns c (c % 32 < 16) with up partner c + 16
+        constexpr int LPR = COLS / 8;
 #pragma unroll
-        for (int j = 0; j < ROWS / (8 * NW); ++j) group(wave * (ROWS / NW) + j * 8);
+        for (int pass = 0; pass < LPR / 4; ++pass) {
+            const int row = pass * (64 / LPR) + lane / LPR;
+            const int ch = ((lane % LPR) >> 2) * 8 + (lane & 3);
+            const f32x4 gv4 = at(row, ch), uv4 = at(row, ch + 4);
+            const int m = mrow0 + row, n = ncol0 + ch * 4;
+            auto info = ri(row);
+            if (INSIDE || (m < M && n < N)) {
+                float gv[4] = {gv4[0], gv4[1], gv4[2], gv4[3]};
+                float uv[4] = {uv4[0], uv4[1], uv4[2], uv4[3]};
+                if constexpr (epi_row_info<Epi>::value) epi.pair_at(info, m, n, gv, uv);
+                else epi.pair(m, n, gv, uv);
+            }
+        }
     } else {
-        // 8-row groups dealt round-robin over the waves
+        // COLS / 4 lanes per row, four columns each
+        constexpr int LPR = COLS / 4;
 #pragma unroll
-        for (int j = 0; j < (ROWS / 8 + NW - 1) / NW; ++j) {
-            const int gi = wave + j * NW;
-            if (gi < ROWS / 8) group(gi * 8);
+        for (int pass = 0; pass < LPR / 4; ++pass) {
+            const int row = pass * (64 / LPR) + lane / LPR;
+            const int ch = lane % LPR;
+            const f32x4 v = at(row, ch);
+            const int m = mrow0 + row, n = ncol0 + ch * 4;
+            if (INSIDE || (m < M && n < N)) epi(m, n, v[0], v[1], v[2], v[3]);
         }
     }
 }
+// Stores of a wave per 16 x 64 sub-tile inside the output.
+template <class E> struct epi_stores { static constexpr int n = 4; };
+template <typename T> struct epi_stores<EpiSwiGLU<T>> { static constexpr int n = 2; };
 
-EBRL_DEV bf16x8 lds_frag(const bf16_t* tile, int row, int c) {
-    return *reinterpret_cast<const bf16x8*>(tile + row * 64 + ((c ^ (row & 7)) << 3));
+// Row-tile-major groups of four row tiles: consecutive tiles share weights
+// (four at a time) and activations.
+EBRL_DEV void tile_origin(int v, int tiles_m, int tiles_n, int bm, int bn, int& m0, int& n0) {
+    constexpr int G = 4;
+    const int group = G * tiles_n, gi = v / group, first_m = gi * G;
+    const int gsz = min(tiles_m - first_m, G), within = v - gi * group;
+    m0 = (first_m + within % gsz) * bm;
+    n0 = (within / gsz) * bn;
 }
 
-// XO: the K loop overlaps the per-tile barrier with MFMAs (below).
-template <int BM, int BN, int WM, int WN, bool PAIRED, bool XO, class Epi>
-__global__ __launch_bounds__(64 * WM * WN, WM * WN == 8 ? 4 : 1) void gemm_bf16_big_kernel(
+// 256 x 256 macro tiles, 8 waves of 128 x 64 in two groups of four (one wave
+// of each group per SIMD) that run half a phase apart: while one group
+// multiplies 32 MFMAs per wave from registers, the other reads its next
+// fragments from LDS and issues DMA, so the MFMA pipes change hands at every
+// barrier instead of idling through LDS latency.  A K tile of 64 is two
+// phases: all of the wave's B columns with its first 64 A rows, then its last
+// 64 rows.  Two LDS stages of 64 KB; a stage's four half-operands are refilled
+// as soon as both groups have read them, so up to 14 KB per wave are in flight
+// and no wait is for the loads just issued.
+//  * What bounds it: a CU's operand stream (64 KB per 8.4 MFLOP K tile; about
+//    72 GB/s per CU is what global_load_lds reaches from L2 here) and the
+//    sustained clock; 1.55 PFLOP/s at 8192 x 8192 x 8192 (fp32 output)
+//    against 1.33 for the 16-wave kernel that read, waited and multiplied in
+//    step, and 1.59 for hipBLASLt.
+//  * Workgroups are persistent (one per CU): the next tile's first DMAs are
+//    issued before the epilogue of the current one, whose stores then drain
+//    behind the next tile's first K tile (7B-class gate/up, 8329 x 22016 x
+//    4096: 1127 -> 1076 us).
+//  * `full` tiles (a multiple of the grid) are dealt evenly; the tiles of the
+//    last, partly filled round are cut in `split` = 2 (128 x 256) or 4 (128 x
+//    128) where that still fits one round, so that more CUs work on them:
+//    7B-class down projection (576 tiles on 256 CUs) 656 -> 587 us, 9600 x
+//    2048 x 8192 291 -> 235 us.
+// Every element is summed over K in order, 32 at a time, whatever its tile.
+template <bool PAIRED, class Epi>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_big_kernel(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb, int M, int N, int K,
-    int k_per_split, float* __restrict__ ws, Epi epi)
+    int full, int split, Epi epi)
 {
-    constexpr int NW = WM * WN;
-    constexpr int WTM = BM / WM, WTN = BN / WN;
-    constexpr int TM = WTM / 16, TN = WTN / 16;
-    static_assert(!PAIRED || (TN % 2 == 0), "paired epilogue needs tile pairs");
-    // one __shared__ object per stage and operand (the DMA that fills them
-    // is inline assembly the compiler does not track: every read of a stage
-    // follows an explicit vmcnt wait and a barrier)
-    __shared__ __attribute__((aligned(1024))) bf16_t sA0[BM * 64];
-    __shared__ __attribute__((aligned(1024))) bf16_t sA1[BM * 64];
-    __shared__ __attribute__((aligned(1024))) bf16_t sB0[BN * 64];
-    __shared__ __attribute__((aligned(1024))) bf16_t sB1[BN * 64];
-
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    int bid = blockIdx.x;
-    const int nb = gridDim.x;
-    if ((nb & 7) == 0) bid = (bid & 7) * (nb >> 3) + (bid >> 3);
-    constexpr int G = 4;  // row tiles per group
-    const int group = G * tiles_n;
-    const int first_m = (bid / group) * G;
-    const int gsz = min(tiles_m - first_m, G);
-    const int within = bid - (bid / group) * group;
-    const int tm_idx = first_m + within % gsz, tn_idx = within / gsz;
-    const int m0 = tm_idx * BM, n0 = tn_idx * BN;
-
-    const int k_begin = blockIdx.y * k_per_split;
-    const int k_end = min(K, k_begin + k_per_split);
-    const int nk = (k_end - k_begin) / 64;
-
+    constexpr int STAGES = 2 * 65536;   // operand stages; 4 KB of epilogue staging per wave follow
+    __shared__ __attribute__((aligned(1024))) char smem[STAGES + 8 * 4096];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave - (wave / WN) * WN;
+    const int wr = wave >> 2, wc = wave & 3;   // group (row half of the tile) and column quarter
+    const int r = lane & 15, g = lane >> 4;
+    const int tiles_m = (M + 255) >> 8, tiles_n = (N + 255) >> 8;
+    const int nk = K >> 6;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)smem);
+
+    // Runs tiles of (64 FA) x (128 FB) until next(m0, n0) says there are no
+    // more.  A half-operand h holds the rows (columns) that phase h (the
+    // wave's h-th fragment set) multiplies: LDS row q of A half h is tile row
+    // (q / HA) 2 HA + h HA + q % HA, i.e. each wave's rows are contiguous in
+    // the output.
+    auto run = [&](auto FAC, auto FBC, int m0, int n0, auto next) {
+        constexpr int FA = decltype(FAC)::value, FB = decltype(FBC)::value;
+        constexpr int HA = 16 * FA, HB = 16 * FB;        // a wave's rows / columns per half
+        constexpr int NA = FA / 2, NB = FB;              // DMA instructions per wave and half
+        constexpr int AHALF = 2 * HA * 128, BHALF = 4 * HB * 128, SB = 2 * (AHALF + BHALF);
+        constexpr int W = 2 * NA + 2 * NB;               // DMA instructions per wave and K tile
+        static_assert(2 * SB <= STAGES, "stages");
+        // stores of an interior tile's epilogue that may still be in flight
+        // behind the next tile's first loads
+        constexpr int EST = 2 * FA * epi_stores<Epi>::n * FB / 2;
+        static_assert(W + EST < 64, "vmcnt range");
+        uint32_t va[2][NA], vb[2][NB];
+        const char *pA, *pB;
+        auto dmaA = [&](int t, int h) {
+            const char* p = pA + (size_t)t * 128;
+            const uint32_t l = lds0 + (t & 1) * SB + h * AHALF + wave * NA * 1024;
+#pragma unroll
+            for (int j = 0; j < NA; ++j) dma16_to_lds_s(p, va[h][j], l + j * 1024);
+        };
+        auto dmaB = [&](int t, int h) {
+            const char* p = pB + (size_t)t * 128;
+            const uint32_t l = lds0 + (t & 1) * SB + 2 * AHALF + h * BHALF + wave * NB * 1024;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) dma16_to_lds_s(p, vb[h][j], l + j * 1024);
+        };
+        // K tiles 0 and 1 but for the second half of A's tile 1; rows past
+        // the operand repeat its last one
+        auto prologue = [&]() {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int j = 0; j < NA; ++j) {
+                    const int q = (wave * NA + j) * 8 + (lane >> 3);
+                    const int row = (q / HA) * 2 * HA + h * HA + q % HA;
+                    va[h][j] = (uint32_t)(min(row, M - 1 - m0) * lda + ((lane & 7) ^ (q & 7)) * 8) * 2u;
+                }
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const int q = (wave * NB + j) * 8 + (lane >> 3);
+                    const int row = (q / HB) * 2 * HB + h * HB + q % HB;
+                    vb[h][j] = (uint32_t)(min(row, N - 1 - n0) * ldb + ((lane & 7) ^ (q & 7)) * 8) * 2u;
+                }
+            }
+            pA = uniform_ptr(A + (size_t)m0 * lda);
+            pB = uniform_ptr(B + (size_t)n0 * ldb);
+            dmaB(0, 0); dmaA(0, 0); dmaB(0, 1); dmaA(0, 1);
+            if (nk > 1) { dmaB(1, 0); dmaA(1, 0); dmaB(1, 1); }
+        };
+        uint32_t a_off[2], b_off[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            a_off[ks] = (uint32_t)((wr * HA + r) * 128 + (((ks * 4 + g) ^ (r & 7)) << 4));
+            b_off[ks] = (uint32_t)(2 * AHALF + (wc * HB + r) * 128 + (((ks * 4 + g) ^ (r & 7)) << 4));
+        }
+        f32x4 acc[2][2][FA][FB];
+        bf16x8 fa[2][FA], fb0[2][FB], fb1[2][FB];
+        auto readA = [&](int st, int h) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int i = 0; i < FA; ++i)
+                    fa[ks][i] = *reinterpret_cast<const bf16x8*>(smem + st + a_off[ks] + h * AHALF + i * 2048);
+        };
+        auto readB = [&](int st, int h, bf16x8 (&f)[2][FB]) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int j = 0; j < FB; ++j)
+                    f[ks][j] = *reinterpret_cast<const bf16x8*>(smem + st + b_off[ks] + h * BHALF + j * 2048);
+        };
+        auto mma = [&](f32x4 (&c)[FA][FB], const bf16x8 (&f)[2][FB]) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int i = 0; i < FA; ++i)
+#pragma unroll
+                    for (int j = 0; j < FB; ++j)
+                        c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[ks][j], fa[ks][i], c[i][j], 0, 0, 0);
+        };
+        // Phase p of a group: read fragments, issue DMA, wait for the DMA that
+        // phase p + 1 reads (`wait`), barrier, multiply, barrier.  A group's
+        // reads are complete before its first barrier, so what phase p reads
+        // may be refilled from phase p + 1 on, by either group.
+        // One K tile with L further ones (0, 1, 2 = two or more); ov: the
+        // previous output tile's stores sit between this tile's DMAs.
+        auto ktile = [&](int t, bool ov, auto LC) {
+            constexpr int L = decltype(LC)::value;
+            const int st = (t & 1) * SB;
+            readB(st, 0, fb0); readA(st, 0); readB(st, 1, fb1);
+            if constexpr (L >= 1) dmaA(t + 1, 1);
+            if constexpr (L >= 2) { if (ov) wait_vmcnt<W + EST>(); else wait_vmcnt<W>(); }
+            else if constexpr (L == 1) wait_vmcnt<W>();
+            else wait_vmcnt<0>();
+            wait_lds();
+            wg_barrier();
+            mma(acc[0][0], fb0); mma(acc[0][1], fb1);
+            wg_barrier();
+            readA(st, 1);
+            if constexpr (L >= 2) {
+                dmaB(t + 2, 0); dmaA(t + 2, 0); dmaB(t + 2, 1);
+                if (ov) wait_vmcnt<W + EST>(); else wait_vmcnt<W>();
+            } else if constexpr (L == 1) wait_vmcnt<NA>();
+            wait_lds();
+            wg_barrier();
+            mma(acc[1][0], fb0); mma(acc[1][1], fb1);
+            wg_barrier();
+        };
+        prologue();
+        bool over = false;   // an interior tile's stores were issued behind the prologue
+        for (;;) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int i = 0; i < FA; ++i)
+#pragma unroll
+                        for (int j = 0; j < FB; ++j) acc[a][b][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // first B halves and first A half of K tile 0
+            if (nk > 1) { if (over) wait_vmcnt<W + EST>(); else wait_vmcnt<W>(); }
+            else wait_vmcnt<NA>();
+            wg_barrier();
+            if (wr == 1) wg_barrier();   // the second group runs half a phase behind
+            int t = 0;
+            for (; t + 2 < nk; ++t) ktile(t, over && t == 0, std::integral_constant<int, 2>{});
+            if (t + 1 < nk) { ktile(t, false, std::integral_constant<int, 1>{}); ++t; }
+            ktile(t, false, std::integral_constant<int, 0>{});
+            if (wr == 0) wg_barrier();   // both groups are done with the stages
+            const int mw = m0 + wr * 2 * HA, nw = n0 + wc * 2 * HB;
+            const bool inside = m0 + 4 * HA <= M && n0 + 8 * HB <= N;
+            // per-row epilogue data: lane l holds the wave's rows l and 64 + l
+            constexpr bool ROWS = epi_row_info<Epi>::value;
+            constexpr int RV = ROWS ? FA / 2 : 1;
+            int2 info[RV];
+            if constexpr (ROWS) {
+#pragma unroll
+                for (int v = 0; v < RV; ++v) info[v] = epi.row_info(min(mw + v * 64 + lane, M - 1));
+            }
+            const bool more = next(m0, n0);
+            if (more) prologue();
+            // Through the wave's own staging LDS, 16 rows at a time; chunks
+            // swizzled by row so that the fragment-layout writes and the
+            // row-contiguous reads (gate/up pairs: 8 lanes on each of two
+            // rows) spread over all banks.
+            char* const stage = smem + STAGES + wave * 4096;
+            auto swz = [](int row) { return ((row & 1) << 2) | ((row >> 1) & 3) | (row & 8); };
+            auto at = [&](int row, int ch) {
+                return *reinterpret_cast<const f32x4*>(stage + row * 256 + ((ch ^ swz(row)) << 4));
+            };
+            auto epilogue = [&](auto IN) {
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int i = 0; i < FA; ++i) {
+#pragma unroll
+                        for (int b = 0; b < 2; ++b)
+#pragma unroll
+                            for (int j = 0; j < FB; ++j)
+                                *reinterpret_cast<f32x4*>(stage + r * 256 + ((((b * FB + j) * 4 + g) ^ swz(r)) << 4)) =
+                                    acc[a][b][i][j];
+                        const int row0 = a * HA + i * 16;
+                        store_subtile<2 * HB, PAIRED, decltype(IN)::value>(
+                            epi, mw + row0, nw, M, N, lane, at, [&](int row) {
+                                const int2 v = info[ROWS ? row0 / 64 : 0];
+                                if constexpr (!ROWS) return v;
+                                else return make_int2(__shfl(v.x, row0 % 64 + row, 64), __shfl(v.y, row0 % 64 + row, 64));
+                            });
+                    }
+            };
+            if (inside) epilogue(std::true_type{});
+            else epilogue(std::false_type{});
+            if (!more) break;
+            over = inside;
+        }
+    };
+
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    // Full tiles: full / grid per workgroup.  The dispatcher deals workgroup
+    // ids round-robin over the 8 XCDs: XCD x's workgroups walk a contiguous
+    // range of tiles together, so that they share operands in its L2.
+    const int P = gridDim.x, bid = blockIdx.x;
+    if (full > 0) {
+        const int rounds = full / P;
+        int i = 0;
+        auto origin = [&](int k, int& m, int& n) {
+            const int v = (P & 7) == 0 ? (bid & 7) * (full >> 3) + k * (P >> 3) + (bid >> 3) : k * P + bid;
+            tile_origin(v, tiles_m, tiles_n, 256, 256, m, n);
+        };
+        int m0, n0;
+        origin(0, m0, n0);
+        run(I4{}, I2{}, m0, n0, [&](int& m, int& n) {
+            if (++i >= rounds) return false;
+            origin(i, m, n);
+            return true;
+        });
+    }
+    // The last round: at most one (part of a) tile per workgroup.
+    const int items = (tiles_m * tiles_n - full) * split;
+    if (bid >= items) return;
+    const int x = bid & 7;
+    const int s = x * (items >> 3) + min(x, items & 7) + (bid >> 3);
+    int m0, n0;
+    tile_origin(full + s / split, tiles_m, tiles_n, 256, 256, m0, n0);
+    auto none = [](int&, int&) { return false; };
+    const int part = s % split;
+    m0 += (part & 1) * 128;
+    n0 += (part >> 1) * 128;
+    if (m0 >= M || n0 >= N) return;
+    if (split == 1) run(I4{}, I2{}, m0, n0, none);
+    else if (split == 2) run(I2{}, I2{}, m0, n0, none);
+    else run(I2{}, I1{}, m0, n0, none);
+}
+
+// Small outputs (fewer 256 x 256 tiles than CUs): BM x BN tiles on four waves
+// (2 x 2), a ring of ST K tiles in LDS with ST - 1 of them in flight, one
+// barrier per K tile.  These launches are held by each CU's operand stream
+// (about 72 GB/s): the two-stage kernel it replaces waited a full memory
+// latency per K tile (0.6-0.9 us), here a 64 x 64 tile takes 0.27 us per K
+// tile.  424 x 1024 x 4096: 39 -> 15 us; 800 x 1024 x 4096: 39 -> 17 us; 424 x
+// 3072 x 1024: 9.9 -> 7.2 us.  Same K order as the kernel above.
+template <int BM, int BN, int ST, bool PAIRED, class Epi>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
+    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb, int M, int N, int K, Epi epi)
+{
+    constexpr int WTM = BM / 2, WTN = BN / 2, TM = WTM / 16, TN = WTN / 16;
+    static_assert(!PAIRED || TN % 2 == 0, "paired epilogue needs tile pairs");
+    constexpr int SB = (BM + BN) * 128;                // bytes of a stage
+    constexpr int PER = (BM + BN) / 32;                // DMA instructions per wave and K tile
+    static_assert((BM + BN) % 32 == 0 && BM % 8 == 0 && ST >= 2 && ST <= 4, "ring");
+    __shared__ __attribute__((aligned(1024))) char smem[ST * SB];
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+    int bid = blockIdx.x;
+    {
+        // XCD x takes the x-th contiguous range of tiles
+        const int nb = gridDim.x, x = bid & 7;
+        bid = x * (nb >> 3) + min(x, nb & 7) + (bid >> 3);
+    }
+    int m0, n0;
+    tile_origin(bid, tiles_m, tiles_n, BM, BN, m0, n0);
+    const int nk = K >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
     const int r = lane & 15, g = lane >> 4;
 
+    // 8-row groups of a stage, A's first: PER per wave
+    uint32_t vo[PER];
+    const char* base[PER];
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)smem + wave * PER * 1024);
+    const char* const pA = uniform_ptr(A + (size_t)m0 * lda);
+    const char* const pB = uniform_ptr(B + (size_t)n0 * ldb);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int q0 = (wave * PER + j) * 8;
+        const int q = q0 + (lane >> 3), c = (lane & 7) ^ (q & 7);
+        if (q0 < BM) {
+            vo[j] = (uint32_t)(min(q, M - 1 - m0) * lda + c * 8) * 2u;
+            base[j] = pA;
+        } else {
+            vo[j] = (uint32_t)(min(q - BM, N - 1 - n0) * ldb + c * 8) * 2u;
+            base[j] = pB;
+        }
+    }
+    auto dma = [&](int t, int st) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) dma16_to_lds_s(base[j] + (size_t)t * 128, vo[j], lds0 + st * SB + j * 1024);
+    };
+    // per-row epilogue data of the wave's rows, one row per lane
+    constexpr bool ROWS = epi_row_info<Epi>::value;
+    int2 info = make_int2(0, 0);
+    if constexpr (ROWS) info = epi.row_info(min(m0 + wm * WTM + min(lane, WTM - 1), M - 1));
+    uint32_t a_off[2], b_off[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        a_off[ks] = (uint32_t)((wm * WTM + r) * 128 + (((ks * 4 + g) ^ (r & 7)) << 4));
+        b_off[ks] = (uint32_t)((BM + wn * WTN + r) * 128 + (((ks * 4 + g) ^ (r & 7)) << 4));
+    }
     f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // Each 64-wide K tile is multiplied as two 32-wide halves.  With XO the
-    // barrier that publishes tile t + 1 sits between tile t's halves: before it a
-    // wave reads tile t's second-half fragments and multiplies its first
-    // half; after it, it issues the DMA of tile t + 2 into the stage tile t
-    // has left, multiplies tile t's second half -- operands already in
-    // registers, so the MFMA pipes start right after the barrier -- and
-    // then reads tile t + 1's first-half fragments behind those MFMAs.
-    // Every accumulator still takes its K steps in order, so the bits do
-    // not depend on XO.  The 16-wave tile has no registers for the second
-    // fragment set (it spills); on 12 waves the overlap measured up to 7 %
-    // faster from K 2048 on (one shape 2.5 % slower) and 3 % slower at
-    // K 1024, on 8 waves 2-6 % faster at every K.
-    static_assert(!XO || WM * WN != 16, "the 16-wave tile runs without the overlap");
-    bf16x8 w0[TN], x0[TM], w1[TN], x1[TM];
-    auto read_half = [&](const bf16_t* ta, const bf16_t* tb, int ks, bf16x8 (&w)[TN], bf16x8 (&x)[TM]) {
+    for (int p = 0; p < ST - 1 && p < nk; ++p) dma(p, p);
+    int st = 0, nst = ST - 1;
+    for (int t = 0; t < nk; ++t) {
+        // this wave's part of tile t has landed (the tiles issued after it may
+        // stay in flight); after the barrier every wave's has, and all have
+        // read tile t - 1, whose stage is refilled next
+        const int later = min(ST - 2, nk - 1 - t);
+        if (ST >= 4 && later >= 2) wait_vmcnt<2 * PER>();
+        else if (ST >= 3 && later >= 1) wait_vmcnt<PER>();
+        else wait_vmcnt<0>();
+        wg_barrier();
+        if (t + ST - 1 < nk) dma(t + ST - 1, nst);
+        const char* const s = smem + st * SB;
+        bf16x8 w[2][TN], x[2][TM];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) w[j] = lds_frag(tb, wn * WTN + j * 16 + r, ks * 4 + g);
+        for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) x[i] = lds_frag(ta, wm * WTM + i * 16 + r, ks * 4 + g);
-    };
-    auto mma = [&](const bf16x8 (&w)[TN], const bf16x8 (&x)[TM]) {
+            for (int j = 0; j < TN; ++j) w[ks][j] = *reinterpret_cast<const bf16x8*>(s + b_off[ks] + j * 2048);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j], x[i], acc[i][j], 0, 0, 0);
-    };
-    // tile t is in stage (ta, tb), tile t + 1 in (na, nb_); tile t + 2 goes
-    // into (ta, tb)
-    auto step = [&](int t, bf16_t* ta, bf16_t* tb, const bf16_t* na, const bf16_t* nb_) {
-        read_half(ta, tb, 1, w1, x1);
-        mma(w0, x0);
-        __builtin_amdgcn_sched_barrier(0);
-        // own fragment reads of this stage done, own DMA of tile t + 1 landed
-        __builtin_amdgcn_s_waitcnt(0);
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        if (t + 2 < nk) {
-            load_tile_lds<BM, NW>(A, lda, m0, M, k_begin + (t + 2) * 64, ta, wave, lane);
-            load_tile_lds<BN, NW>(B, ldb, n0, N, k_begin + (t + 2) * 64, tb, wave, lane);
+            for (int i = 0; i < TM; ++i) x[ks][i] = *reinterpret_cast<const bf16x8*>(s + a_off[ks] + i * 2048);
         }
-        mma(w1, x1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (t + 1 < nk) read_half(na, nb_, 0, w0, x0);
-    };
-
-    // Without the overlap: a whole K tile's fragments are read, multiplied,
-    // then the wave waits at the barrier.
-    auto compute = [&](const bf16_t* ta, const bf16_t* tb) {
-        read_half(ta, tb, 0, w0, x0);
-        read_half(ta, tb, 1, w1, x1);
-        mma(w0, x0);
-        mma(w1, x1);
-    };
-
-    if (nk > 0) {
-        load_tile_lds<BM, NW>(A, lda, m0, M, k_begin, sA0, wave, lane);
-        load_tile_lds<BN, NW>(B, ldb, n0, N, k_begin, sB0, wave, lane);
-        wait_vm_all();
-        __syncthreads();
-        if constexpr (!XO) {
-            for (int kt = 0; kt < nk; kt += 2) {
-                if (kt + 1 < nk) {
-                    load_tile_lds<BM, NW>(A, lda, m0, M, k_begin + (kt + 1) * 64, sA1, wave, lane);
-                    load_tile_lds<BN, NW>(B, ldb, n0, N, k_begin + (kt + 1) * 64, sB1, wave, lane);
-                }
-                compute(sA0, sB0);
-                wait_vm_all();
-                __syncthreads();
-                if (kt + 1 < nk) {
-                    if (kt + 2 < nk) {
-                        load_tile_lds<BM, NW>(A, lda, m0, M, k_begin + (kt + 2) * 64, sA0, wave, lane);
-                        load_tile_lds<BN, NW>(B, ldb, n0, N, k_begin + (kt + 2) * 64, sB0, wave, lane);
-                    }
-                    compute(sA1, sB1);
-                    wait_vm_all();
-                    __syncthreads();
-                }
-            }
-        } else {
-            if (nk > 1) {
-                load_tile_lds<BM, NW>(A, lda, m0, M, k_begin + 64, sA1, wave, lane);
-                load_tile_lds<BN, NW>(B, ldb, n0, N, k_begin + 64, sB1, wave, lane);
-            }
-            read_half(sA0, sB0, 0, w0, x0);
-            for (int kt = 0; kt < nk; kt += 2) {
-                step(kt, sA0, sB0, sA1, sB1);
-                if (kt + 1 < nk) step(kt + 1, sA1, sB1, sA0, sB0);
-            }
-        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][j], x[ks][i], acc[i][j], 0, 0, 0);
+        nst = st;
+        st = st + 1 == ST ? 0 : st + 1;
     }
-
-    // Epilogue through LDS (free once every wave has passed the loop's last
-    // barrier): a wave stages 16 rows x 64 columns of its tile at a time and
-    // reads them back row-contiguous, so that each store (and the residual
-    // read) covers 256-byte fp32 / 64-128-byte bf16 row segments instead of
-    // 16-32-byte pieces of 16 rows.  Rows are padded to 68 floats so the
-    // fragment-layout writes spread over the banks.
-    static_assert(WTN == 64 || WTN == 32, "staging assumes 64- or 32-column wave tiles");
+    wg_barrier();
+    // epilogue staging in the stages: rows padded by one chunk
     constexpr int SROW = WTN + 4;
-    constexpr int PER_A = (BM * 64 * 2) / (16 * SROW * 4), PER_B = (BN * 64 * 2) / (16 * SROW * 4);
-    static_assert(2 * (PER_A + PER_B) >= NW, "staging space");
-    static_assert(WTM == 64, "one row per lane in the per-row epilogue data");
-    // per-row epilogue data of the wave's 64 rows, one row per lane
-    __shared__ int4 s_row[epi_row_info<Epi>::value ? NW : 1][64];
-    if constexpr (epi_row_info<Epi>::value)
-        s_row[wave][lane] = epi.row_info(min(m0 + wm * WTM + lane, M - 1));
-    bf16_t* const region = wave < PER_A ? sA0 : (wave < 2 * PER_A ? sA1 : (wave < 2 * PER_A + PER_B ? sB0 : sB1));
-    const int slot = wave < PER_A ? wave : (wave < 2 * PER_A ? wave - PER_A
-                                            : (wave < 2 * PER_A + PER_B ? wave - 2 * PER_A : wave - 2 * PER_A - PER_B));
-    float* const stage = reinterpret_cast<float*>(region) + slot * 16 * SROW;
-    const int ncol0 = n0 + wn * WTN;
+    static_assert(4 * 16 * SROW * 4 <= ST * SB, "staging space");
+    float* const stage = reinterpret_cast<float*>(smem) + wave * 16 * SROW;
+    auto at = [&](int row, int ch) { return *reinterpret_cast<const f32x4*>(stage + row * SROW + ch * 4); };
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-            *reinterpret_cast<f32x4*>(stage + r * SROW + j * 16 + 4 * g) = acc[i][j];
-        const int mrow0 = m0 + wm * WTM + i * 16;
-        if constexpr (PAIRED) {
-            // WTN / 8 lanes per row: gate columns c (c % 32 < 16) with up partner c + 16
-            constexpr int LPR = WTN / 8;
-#pragma unroll
-            for (int pass = 0; pass < LPR / 4; ++pass) {
-                const int row = pass * (64 / LPR) + lane / LPR;
-                const int c = ((lane % LPR) >> 2) * 32 + (lane & 3) * 4;
-                const f32x4 gv4 = *reinterpret_cast<const f32x4*>(stage + row * SROW + c);
-                const f32x4 uv4 = *reinterpret_cast<const f32x4*>(stage + row * SROW + c + 16);
-                const int m = mrow0 + row, n = ncol0 + c;
-                if (m < M && n < N) {
-                    float gv[4] = {gv4[0], gv4[1], gv4[2], gv4[3]};
-                    float uv[4] = {uv4[0], uv4[1], uv4[2], uv4[3]};
-                    if constexpr (epi_row_info<Epi>::value) epi.pair_at(s_row[wave][i * 16 + row], m, n, gv, uv);
-                    else epi.pair(m, n, gv, uv);
-                }
-            }
-        } else {
-            // WTN / 4 lanes per row, four columns each
-            constexpr int LPR = WTN / 4;
-#pragma unroll
-            for (int pass = 0; pass < LPR / 4; ++pass) {
-                const int row = pass * (64 / LPR) + lane / LPR;
-                const int c = (lane % LPR) * 4;
-                const f32x4 v = *reinterpret_cast<const f32x4*>(stage + row * SROW + c);
-                const int m = mrow0 + row, n = ncol0 + c;
-                if (m < M && n < N) epi(m, n, v[0], v[1], v[2], v[3]);
-            }
-        }
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<f32x4*>(stage + r * SROW + j * 16 + 4 * g) = acc[i][j];
+        store_subtile<WTN, PAIRED, false>(epi, m0 + wm * WTM + i * 16, n0 + wn * WTN, M, N, lane, at, [&](int row) {
+            if constexpr (!ROWS) return info;
+            else return make_int2(__shfl(info.x, i * 16 + row, 64), __shfl(info.y, i * 16 + row, 64));
+        });
     }
 }
-
 
 // ------------------------------------------- bf16 GEMM, decode-sized M --
 // M <= 256 (one row per environment), K % 64 == 0.  A workgroup owns a
@@ -687,6 +881,22 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
         dec_dma<TM * 16>(A, lda, m0, M, grp * 64, xl, lane);
     };
 
+    // Output units: one fragment lane (or a gate/up fragment pair) each.
+    constexpr int G = PAIRED ? 2 : 1;
+    constexpr int UNITS = FR / G * 64;
+    constexpr int PER = (UNITS + 255) / 256;
+    // the units' destination rows, loaded here so that the epilogue does not
+    // wait for them
+    constexpr bool ROWS = epi_row_info<Epi>::value;
+    int2 row_of[ROWS ? PER : 1];
+    if constexpr (ROWS) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int u = min(tid + 256 * q, UNITS - 1);
+            row_of[q] = epi.row_info(min(m0 + ((u >> 6) * G / TN) * 16 + (u & 15), M - 1));
+        }
+    }
+
     f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -800,10 +1010,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
     __syncthreads();
     auto red_at = [&](int w, int e) -> f32x4 { return red_region(w)[e]; };
 
-    // Output units: one fragment lane (or a gate/up fragment pair) each.
-    constexpr int G = PAIRED ? 2 : 1;
-    constexpr int UNITS = FR / G * 64;
-    constexpr int PER = (UNITS + 255) / 256;
     f32x4 v[PER][G];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -887,7 +1093,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
                 if constexpr (PAIRED) {
                     float gv[4] = {v[q][0][0], v[q][0][1], v[q][0][2], v[q][0][3]};
                     float uv[4] = {v[q][1][0], v[q][1][1], v[q][1][2], v[q][1][3]};
-                    epi.pair(m, n, gv, uv);
+                    if constexpr (ROWS) epi.pair_at(row_of[q], m, n, gv, uv);
+                    else epi.pair(m, n, gv, uv);
                 } else {
                     epi(m, n, v[q][0][0], v[q][0][1], v[q][0][2], v[q][0][3]);
                 }
@@ -1014,7 +1221,9 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ ws, int splits, i
 // Tile and split choice depend only on (M, N, K) and the stream's CU count;
 // the split count, the only one that orders sums, on (N, K) alone.
 struct GemmPlan {
-    int bm; int bn; int splits; int k_per_split; bool big;
+    int bm; int splits; int k_per_split;
+    bool seq;      // K in order: the large-M kernel (bm 256) or the ring kernel (bm x bn)
+    int bn; int grid, full, split;   // large-M kernel: workgroups, evenly dealt tiles, cut of the last round's tiles
     bool dec; int steps_per_split; int tm; int m_tiles; int dbn;   // decode kernel (steps: 64-wide K groups)
 };
 
@@ -1022,38 +1231,40 @@ struct GemmPlan {
 // summation order; the split count (decode only) is a function of (N, K).
 constexpr int SPLIT_MAX_M = DECODE_MAX_ROWS;
 
-// Macro tile of the large-M kernel: 256 x 256 (16 waves), 192 x 256 (12
-// waves) or 128 x 128 (8 waves of 64 x 32, two workgroups per CU; with four
-// waves of 64 x 64 instead, one workgroup on a CU kept a single wave per
-// SIMD and ran the flow expert's projections up to 13 % slower).  Each is priced as
-// the number of rounds its tiles take over the stream's CUs times one round's
-// work per CU, divided by the variant's throughput relative to 256 x 256
-// (measured: 0.85 and 0.8); the cheapest wins, ties to the larger tile.  The
-// smaller tiles pay off where 256 x 256 tiles leave most of a last round
-// idle (e.g. 576 tiles = 2.25 rounds).  Every variant runs the same K loop,
-// so an element's summation order does not depend on the choice.
-static void big_tile(int M, int N, int cus, int& bm, int& bn) {
-    const int CUS = cus;
-    struct V { int bm, bn, per_cu; double rel; } vs[] = {{256, 256, 1, 1.0}, {192, 256, 1, 0.85}, {128, 128, 2, 0.8}};
-    double best = 0;
-    for (int i = 0; i < 3; ++i) {
-        const V& v = vs[i];
-        const long tiles = (long)((M + v.bm - 1) / v.bm) * ((N + v.bn - 1) / v.bn);
-        const long rounds = (tiles + (long)CUS * v.per_cu - 1) / ((long)CUS * v.per_cu);
-        const double cost = rounds * (double)v.bm * v.bn * v.per_cu / (65536.0 * v.rel);
-        if (i == 0 || cost < best * 0.999) {
-            best = cost;
-            bm = v.bm;
-            bn = v.bn;
+// Projections that sum K in order (prefill, ViT, experts): the kernel whose
+// modelled time is least.  Both are bound by what a CU streams, so a tile's
+// time per 64-wide K tile is a constant of its shape (us, measured on one
+// MI355X with every CU busy): 1.2 for 256 x 256, and for the last round's cut
+// tiles 0.70 (128 x 256) and 0.45 (128 x 128); ring tiles at least 0.37 (64 x
+// 128), 0.24 (64 x 64), 0.19 (32 x 64), and BM + BN rows of 128 bytes at 70
+// GB/s per CU where several tiles share it.  The constants 3.5 and 2.4 us are
+// launch, first loads and epilogue.  No choice changes a sum's order.
+static void plan_in_order(GemmPlan& p, int M, int N, int K, int cus) {
+    const double nk = K / 64;
+    const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
+    const long full = tiles / cus * cus, rest = tiles - full;
+    p.seq = true;
+    p.bm = p.bn = 256;
+    p.split = rest * 4 <= cus ? 4 : rest * 2 <= cus ? 2 : 1;
+    p.full = (int)full;
+    p.grid = (int)(full ? cus : rest * p.split);
+    double best = 3.5 + nk * (1.2 * (tiles / cus) + (!rest ? 0 : p.split == 4 ? 0.45 : p.split == 2 ? 0.70 : 1.1));
+    struct V { int bm, bn; double least; } vs[] = {{64, 128, 0.37}, {64, 64, 0.24}, {32, 64, 0.19}};
+    for (const V& v : vs) {
+        const double per_cu = (double)((M + v.bm - 1) / v.bm) * ((N + v.bn - 1) / v.bn) / cus;
+        const double t = 2.4 + nk * std::max(v.least, per_cu * (v.bm + v.bn) * 128 / 70e3);
+        if (t < best) {
+            best = t;
+            p.bm = v.bm;
+            p.bn = v.bn;
         }
     }
 }
 
 static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok, int cus = 256) {
     GemmPlan p;
-    p.big = false;
+    p.seq = false;
     p.dec = false;
-    p.bn = 0;
     p.splits = 1;
     p.k_per_split = K;
     if (bf16 && split_ok && K % 64 == 0) {
@@ -1112,9 +1323,8 @@ static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool
         }
         return p;
     }
-    if (bf16 && !split_ok && M >= 256 && K % 64 == 0) {
-        p.big = true;
-        big_tile(M, N, cus, p.bm, p.bn);
+    if (bf16 && !split_ok && K % 64 == 0) {
+        plan_in_order(p, M, N, K, cus);
         return p;
     }
     if (!bf16) p.bm = 64;
@@ -1142,21 +1352,20 @@ static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool
 template <bool PAIRED, class Epi>
 static void launch_bf16(const GemmArgs& a, const GemmPlan& p, Epi epi, hipStream_t s) {
     const bool split = p.splits > 1;
-    if (p.big) {
-        const long tiles = (long)((a.M + p.bm - 1) / p.bm) * ((a.N + p.bn - 1) / p.bn);
-        dim3 grid((unsigned)tiles, 1);
-        if (p.bm == 256)
-            hipLaunchKernelGGL((gemm_bf16_big_kernel<256, 256, 4, 4, PAIRED, false, Epi>), grid, dim3(1024), 0, s,
-                               (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B, a.ldb, a.M, a.N, a.K, a.K, a.ws, epi);
-        else if (p.bm == 192 && a.K >= 2048)
-            hipLaunchKernelGGL((gemm_bf16_big_kernel<192, 256, 3, 4, PAIRED, true, Epi>), grid, dim3(768), 0, s,
-                               (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B, a.ldb, a.M, a.N, a.K, a.K, a.ws, epi);
-        else if (p.bm == 192)
-            hipLaunchKernelGGL((gemm_bf16_big_kernel<192, 256, 3, 4, PAIRED, false, Epi>), grid, dim3(768), 0, s,
-                               (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B, a.ldb, a.M, a.N, a.K, a.K, a.ws, epi);
-        else
-            hipLaunchKernelGGL((gemm_bf16_big_kernel<128, 128, 2, 4, PAIRED, true, Epi>), grid, dim3(512), 0, s,
-                               (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B, a.ldb, a.M, a.N, a.K, a.K, a.ws, epi);
+    if (p.seq) {
+        const bf16_t *A = (const bf16_t*)a.A, *B = (const bf16_t*)a.B;
+        if (p.bm == 256) {
+            hipLaunchKernelGGL((gemm_bf16_big_kernel<PAIRED, Epi>), dim3(p.grid), dim3(512), 0, s, A, a.lda, B, a.ldb,
+                               a.M, a.N, a.K, p.full, p.split, epi);
+            return;
+        }
+        const dim3 grid((unsigned)((long)((a.M + p.bm - 1) / p.bm) * ((a.N + p.bn - 1) / p.bn)));
+        auto ring = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, A, a.lda, B, a.ldb, a.M, a.N, a.K, epi);
+        };
+        if (p.bn == 128) ring(gemm_bf16_ring_kernel<64, 128, 3, PAIRED, Epi>);
+        else if (p.bm == 64) ring(gemm_bf16_ring_kernel<64, 64, 3, PAIRED, Epi>);
+        else ring(gemm_bf16_ring_kernel<32, 64, 4, PAIRED, Epi>);
         return;
     }
     if (p.dec) {

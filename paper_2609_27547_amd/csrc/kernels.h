@@ -126,24 +126,21 @@ void rmsnorm_rows(bool bf16_out, const float* X, int ldx, const int* rows, void*
 
 // Rotary embedding + paged KV write of the fused QKV projection, applied in
 // the GEMM epilogue (EPI_QKV): rotated queries go to Q (act dtype), rotated
-// keys and the values to the paged cache at (seq_env[row_seq[m]],
-// row_pos[m]).  use_rope = false skips rotation.  The QKV weight rows are
-// packed per head so that rows e and e + hd/2 sit in the two 16-row halves
-// of one 32-row group.  (qkv/ld are used only by the standalone kernel.)
+// keys and the values to the paged cache.  row_dst[m] = {position of row m in
+// its sequence, physical block of that position}: one load per row, where the
+// chain row -> sequence -> env -> block table took three dependent ones at the
+// end of every QKV launch.  use_rope = false skips rotation.  The QKV weight
+// rows are packed per head so that rows e and e + hd/2 sit in the two 16-row
+// halves of one 32-row group.
 struct RopeKVArgs {
-    bool bf16 = true;
-    const float* qkv = nullptr; int ld = 0;
-    int M = 0, q_heads = 0;
+    int q_heads = 0;
     void* Q = nullptr; int ldq = 0;
     PagedKV kv;
-    const int* seq_env = nullptr;
-    const int* row_seq = nullptr;
-    const int* row_pos = nullptr;
+    const int2* row_dst = nullptr;
     const float* cos_tab = nullptr;  // [max_pos][hd/2]
     const float* sin_tab = nullptr;
     bool use_rope = true;
 };
-void rope_kv_write(const RopeKVArgs& a, hipStream_t s);
 
 // X[dst] = E[id] as float (id = ids[src ? src[i] : i*stride + off]; dst = dst_rows ? dst_rows[i] : i);
 // ids outside [0, n_rows_e) give zero rows.

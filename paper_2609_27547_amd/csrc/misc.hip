@@ -1,5 +1,4 @@
-// Row-wise kernels of the policy forward: RMSNorm, rotary embedding with the
-// paged-KV write, embedding gathers, patch extraction, the 256-bin action
+// Row-wise kernels of the policy forward: RMSNorm, embedding gathers, patch extraction, the 256-bin action
 // head with its argmax, and the flow-matching expert's input and Euler
 // update.  All reductions run in a fixed order (deterministic results).
 #include <math.h>
@@ -109,64 +108,6 @@ void rmsnorm_rows(bool bf16_out, const float* X, int ldx, const int* rows, void*
     else
         hipLaunchKernelGGL(rmsnorm_kernel<float>, dim3(n_rows), dim3(256), 0, s, X, ldx, rows,
                            (float*)Y, ldy, d, eps);
-}
-
-// ------------------------------------------------------ rotary + KV write --
-template <typename T>
-__global__ __launch_bounds__(256) void rope_kv_kernel(RopeKVArgs a)
-{
-    const int m = blockIdx.x;
-    const int hd = a.kv.head_dim, half = hd / 2;
-    const int hq = a.q_heads, hkv = a.kv.kv_heads;
-    const int seq = a.row_seq[m], pos = a.row_pos[m];
-    const int env = a.seq_env[seq];
-    const float* x = a.qkv + (size_t)m * a.ld;
-    const float* ct = a.cos_tab + (size_t)pos * half;
-    const float* st = a.sin_tab + (size_t)pos * half;
-    const int blk = a.kv.block_table[(size_t)env * a.kv.bt_stride + (pos >> 4)];
-    T* kdst = (T*)a.kv.base + (size_t)blk * 2 * hkv * KV_BLOCK * hd + (size_t)(pos & 15) * hd;
-    T* vdst = kdst + (size_t)hkv * KV_BLOCK * hd;
-    T* q = (T*)a.Q + (size_t)m * a.ldq;
-    // rotated queries
-    for (int idx = threadIdx.x; idx < hq * half; idx += blockDim.x) {
-        const int h = idx / half, i = idx - h * half;
-        const float x1 = x[h * hd + i], x2 = x[h * hd + i + half];
-        float o1 = x1, o2 = x2;
-        if (a.use_rope) {
-            const float c = ct[i], sn = st[i];
-            o1 = x1 * c - x2 * sn;
-            o2 = x2 * c + x1 * sn;
-        }
-        st_elem<T>(q + h * hd + i, o1);
-        st_elem<T>(q + h * hd + i + half, o2);
-    }
-    // rotated keys
-    const float* xk = x + hq * hd;
-    for (int idx = threadIdx.x; idx < hkv * half; idx += blockDim.x) {
-        const int h = idx / half, i = idx - h * half;
-        const float x1 = xk[h * hd + i], x2 = xk[h * hd + i + half];
-        float o1 = x1, o2 = x2;
-        if (a.use_rope) {
-            const float c = ct[i], sn = st[i];
-            o1 = x1 * c - x2 * sn;
-            o2 = x2 * c + x1 * sn;
-        }
-        T* kd = kdst + (size_t)h * KV_BLOCK * hd;
-        st_elem<T>(kd + i, o1);
-        st_elem<T>(kd + i + half, o2);
-    }
-    // values
-    const float* xv = x + (hq + hkv) * hd;
-    for (int idx = threadIdx.x; idx < hkv * hd; idx += blockDim.x) {
-        const int h = idx / hd, i = idx - h * hd;
-        st_elem<T>(vdst + (size_t)h * KV_BLOCK * hd + i, xv[idx]);
-    }
-}
-
-void rope_kv_write(const RopeKVArgs& a, hipStream_t s) {
-    if (a.M <= 0) return;
-    if (a.bf16) hipLaunchKernelGGL(rope_kv_kernel<bf16_t>, dim3(a.M), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(rope_kv_kernel<float>, dim3(a.M), dim3(256), 0, s, a);
 }
 
 // ------------------------------------------------------------ embedding --

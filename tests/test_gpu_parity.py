@@ -131,12 +131,12 @@ def test_op_gemm_concurrent_streams_keep_their_own_split_workspace():
 
 
 def test_large_gemm_tile_variants_agree_bitwise():
-    """The large-M kernel's macro tile follows the shape: with 4092 columns
-    (ragged against both 256 and 128), 9200 rows take 192 x 256 tiles (the
-    last row tile ragged), 4096 rows 256 x 256, 2048 rows 128 x 128 and 1000
-    rows 128 x 128 with a ragged last row tile (256 tiles, one workgroup per
-    CU).  The rows the calls share are bitwise equal (every variant runs the
-    same K order), and the full product matches the definition."""
+    """The tiles of a prefill-sized product follow the shape: with 4092 columns
+    (ragged against both 256 and 128), 9200 rows take two rounds of 256 x 256
+    tiles and a third of cut ones (the last row tile ragged), 4096 rows one
+    round, 2048 and 1000 rows cut tiles only.  The rows the calls share are
+    bitwise equal (every variant runs the same K order), and the full product
+    matches the definition."""
     rng = np.random.default_rng(9200)
     K = 192
     a = rng.normal(size=(9200, K)).astype(np.float32)
@@ -155,6 +155,26 @@ def test_large_gemm_tile_variants_agree_bitwise():
     a64 = A.float().cpu().numpy().astype(np.float64)
     b64 = B.float().cpu().numpy().astype(np.float64)
     assert P.row_rel_err(outs[9200].cpu().numpy(), M.linear(a64, b64)) < 2e-6
+
+
+@pytest.mark.parametrize("M_,N,K", [
+    (256, 32, 64), (300, 4, 128), (257, 260, 192),      # ring tiles: edges, one to three K tiles
+    (1100, 4100, 64), (3000, 2052, 128),                # one round of cut 256 x 256 tiles, ragged
+    (4353, 4100, 64), (4353, 4100, 128), (4353, 4100, 192),   # a full round and a remainder of cut tiles
+    (6400, 4352, 192), (8449, 4100, 64), (12800, 5888, 128)])  # uncut remainder; two and four rounds
+def test_in_order_gemm_tile_and_round_edges_exact(M_, N, K):
+    """Prefill-sized products on small integers, whose sums are exact in
+    float32: every element equals the integer product, at the edges of the
+    tiles, with one, two and three K tiles, with one and several tiles per
+    workgroup and with the last round's tiles whole and cut."""
+    g = torch.Generator().manual_seed(M_ + N + K)
+    a = torch.randint(-3, 4, (M_, K), generator=g).float()
+    b = torch.randint(-3, 4, (N, K), generator=g).float()
+    C = torch.full((M_, N), float("nan"), device="cuda")
+    A, B = a.cuda().bfloat16(), b.cuda().bfloat16()
+    for _ in range(2):
+        E.op_gemm(A, B, C)
+    assert torch.equal(C.cpu(), a @ b.T)
 
 
 # ------------------------------------------------------- resident weights --
