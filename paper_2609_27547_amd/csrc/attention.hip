@@ -440,7 +440,9 @@ template <> EBRL_DEV void load8<float>(const float* p, float* o) {
     o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
 }
 
-// grid (n, q_heads, max_splits), 256 threads
+// grid (n, q_heads, max_splits), 256 threads.  With one split (max_splits ==
+// 1: sequences of at most ATTN_DEC_CHUNK keys) its state is the result and is
+// written as the output, which saves the combine launch.
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a, float scale_log2)
 {
@@ -517,9 +519,10 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
     for (int d = tid; d < HD; d += 256) {
         float o = 0.f;
         for (int q = 0; q < KPP; ++q) o += sacc[q * HD + d];
-        part[d] = o;
+        if (a.max_splits == 1) st_elem<T>((T*)a.O + (size_t)i * a.ldo + h * HD + d, o / sml[1]);
+        else part[d] = o;
     }
-    if (tid == 0) { part[HD] = sml[0]; part[HD + 1] = sml[1]; }
+    if (a.max_splits > 1 && tid == 0) { part[HD] = sml[0]; part[HD + 1] = sml[1]; }
 }
 
 // bf16 decode attention.  A sequence of kv_len keys is cut into
@@ -733,10 +736,10 @@ void attn_decode(const AttnDecodeArgs& a, hipStream_t s) {
     } else {
         if (hd == 64) {
             hipLaunchKernelGGL((attn_decode_split_kernel<float, 64>), g1, dim3(256), 0, s, a, scale_log2);
-            hipLaunchKernelGGL((attn_decode_combine_kernel<float, 64>), g2, dim3(64), 0, s, a);
+            if (a.max_splits > 1) hipLaunchKernelGGL((attn_decode_combine_kernel<float, 64>), g2, dim3(64), 0, s, a);
         } else {
             hipLaunchKernelGGL((attn_decode_split_kernel<float, 128>), g1, dim3(256), 0, s, a, scale_log2);
-            hipLaunchKernelGGL((attn_decode_combine_kernel<float, 128>), g2, dim3(128), 0, s, a);
+            if (a.max_splits > 1) hipLaunchKernelGGL((attn_decode_combine_kernel<float, 128>), g2, dim3(128), 0, s, a);
         }
     }
 }

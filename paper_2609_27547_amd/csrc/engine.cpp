@@ -498,20 +498,23 @@ struct BlockCall {
     AttnDecodeArgs dec;
 };
 
-// Decode steps of bf16 policies fold each pre-norm into the projection that
-// follows it: the residual stream's producers (embedding, O and down
-// projections) also store the rows in bf16, and the QKV and gate/up decode
-// GEMMs scale their output rows by the RMSNorm factor of those rows.
-bool fold_decode_norm(const ebrl_policy* p, const StackDims& s, int rows) {
+// Pre-norms folded into the projection that follows them: the QKV and gate/up
+// GEMMs scale their output rows by the RMSNorm factor of their input rows.
+// fp32 policies fold everywhere, reading the residual stream itself; bf16
+// policies in decode steps, where the stream's producers (token embedding, O
+// and down projections) also store the rows in bf16.
+bool fold_norm(const ebrl_policy* p, const StackDims& s, int rows, bool decode) {
     const int qkvn = (s.hq + 2 * s.hkv) * s.hd;
-    return p->bf16 && gemm_row_norm_ok(true, rows, qkvn, s.d, p->ws_floats) &&
+    if (!p->bf16) return true;
+    return decode && gemm_row_norm_ok(true, rows, qkvn, s.d, p->ws_floats) &&
            gemm_row_norm_ok(true, rows, 2 * s.mlp, s.d, p->ws_floats);
 }
 
 int run_block(ebrl_policy* p, BlockCall& b) {
     const StackDims& s = *b.sd;
     const int qn = s.hq * s.hd, qkvn = (s.hq + 2 * s.hkv) * s.hd;
-    const bool fold = b.decode && fold_decode_norm(p, s, b.rows);
+    const bool fold = fold_norm(p, s, b.rows, b.decode);
+    const void* const normed = fold && !p->bf16 ? (const void*)b.R : p->Xn;   // operand of the two projections
     if (!fold) {
         prof_begin(p, EBRL_K_OTHER);
         rmsnorm_rows(p->bf16, b.R, s.d, nullptr, p->Xn, s.d, b.rows, s.d, 1e-6f, p->stream);
@@ -524,7 +527,7 @@ int run_block(ebrl_policy* p, BlockCall& b) {
     r.Q = p->Qb; r.ldq = qn; r.kv = b.kv; r.row_dst = b.row_dst;
     r.cos_tab = p->cos_tab; r.sin_tab = p->sin_tab; r.use_rope = b.use_rope;
     GemmArgs g;
-    g.A = p->Xn; g.lda = s.d; g.B = b.w->qkv; g.ldb = s.d; g.M = b.rows; g.N = qkvn; g.K = s.d;
+    g.A = normed; g.lda = s.d; g.B = b.w->qkv; g.ldb = s.d; g.M = b.rows; g.N = qkvn; g.K = s.d;
     g.epi = EPI_QKV; g.rope = &r; g.row_norm = fold;
     run_gemm(p, g, b.decode);
     if (b.decode) {
@@ -543,7 +546,7 @@ int run_block(ebrl_policy* p, BlockCall& b) {
     g = GemmArgs();
     g.A = p->Ob; g.lda = qn; g.B = b.w->o; g.ldb = qn; g.M = b.rows; g.N = s.d; g.K = qn;
     g.epi = EPI_RESID; g.C = b.R; g.ldc = s.d;
-    if (fold) { g.xb = p->Xn; g.ldxb = s.d; }
+    if (fold && p->bf16) { g.xb = p->Xn; g.ldxb = s.d; }
     run_gemm(p, g, b.decode);
     if (!fold) {
         prof_begin(p, EBRL_K_OTHER);
@@ -551,13 +554,13 @@ int run_block(ebrl_policy* p, BlockCall& b) {
         prof_end(p, 0, (double)b.rows * s.d * (4 + p->esz));
     }
     g = GemmArgs();
-    g.A = p->Xn; g.lda = s.d; g.B = b.w->gu; g.ldb = s.d; g.M = b.rows; g.N = 2 * s.mlp; g.K = s.d;
+    g.A = normed; g.lda = s.d; g.B = b.w->gu; g.ldb = s.d; g.M = b.rows; g.N = 2 * s.mlp; g.K = s.d;
     g.epi = EPI_SWIGLU; g.C = p->Hb; g.ldc = s.mlp; g.row_norm = fold;
     run_gemm(p, g, b.decode);
     g = GemmArgs();
     g.A = p->Hb; g.lda = s.mlp; g.B = b.w->down; g.ldb = s.mlp; g.M = b.rows; g.N = s.d; g.K = s.mlp;
     g.epi = EPI_RESID; g.C = b.R; g.ldc = s.d;
-    if (fold) { g.xb = p->Xn; g.ldxb = s.d; }
+    if (fold && p->bf16) { g.xb = p->Xn; g.ldxb = s.d; }
     run_gemm(p, g, b.decode);
     return EBRL_OK;
 }
@@ -1237,7 +1240,7 @@ int ebrl_prefill(ebrl_policy* p, const ebrl_obs_batch* obs, const int32_t* env_i
     // ---- language tokens
     if (!lang_dst.empty()) {
         prof_begin(p, EBRL_K_OTHER);
-        embed_rows(p->bf16, p->e_lang, c.vocab, c.d, obs->lang_ids, md + o_lsrc, 0, 0, md + o_ldst, p->X, c.d,
+        embed_rows(p->bf16, p->e_lang, c.vocab, c.d, obs->lang_ids, md + o_lsrc, md + o_ldst, p->X, c.d,
                    (int)lang_dst.size(), p->stream);
         prof_end(p, 0, 0);
     }
@@ -1308,21 +1311,20 @@ int ebrl_decode_actions(ebrl_policy* p, const int32_t* env_ids, int32_t n, int32
     // split count of the fp32 attention path: the policy's longest sequence
     const int max_splits = (c.max_seq + steps + ATTN_DEC_CHUNK - 1) / ATTN_DEC_CHUNK;
 
-    const bool fold = fold_decode_norm(p, p->dec, nc);
+    const bool fold = fold_norm(p, p->dec, nc, true);
     auto body = [&]() -> int {
         LogitsArgs la;
         la.bf16 = p->bf16; la.W = p->w_act; la.d = c.d; la.n_bins = c.n_bins; la.n = nc;
         la.tokens = p->dec_tok; la.actions = p->dec_act; la.margins = p->dec_mar; la.ntok = ntok;
         la.lg = p->lg; la.counters = p->lg_counters;
         la.X = p->h_pre; la.ldx = c.d; la.rows = md + o_env; la.col = 0;
+        // the head writes each step's input rows: the chosen tokens' embeddings
+        la.emb = steps > 0 ? p->e_act : nullptr;
+        la.nx = p->X; la.ldnx = c.d; la.nxb = fold && p->bf16 ? p->Xn : nullptr; la.ldnxb = c.d;
         prof_begin(p, EBRL_K_OTHER);
         action_logits(la, p->stream);
         prof_end(p, 0, (double)c.n_bins * c.d * p->esz);
         for (int k = 1; k <= steps; ++k) {
-            prof_begin(p, EBRL_K_OTHER);
-            embed_rows(p->bf16, p->e_act, c.n_bins, c.d, p->dec_tok, nullptr, ntok, k - 1, nullptr, p->X, c.d, nc,
-                       p->stream, fold ? p->Xn : nullptr, c.d);
-            prof_end(p, 0, 0);
             double kv_bytes = 0;
             for (int i = 0; i < nc; ++i) kv_bytes += (double)(p->envs[seq_env[i]].T + k);
             kv_bytes *= 2.0 * c.kv_heads * c.head_dim * p->esz;
@@ -1339,6 +1341,7 @@ int ebrl_decode_actions(ebrl_policy* p, const int32_t* env_ids, int32_t n, int32
                 if (rc2) return rc2;
             }
             la.X = p->X; la.rows = nullptr; la.col = k;
+            if (k == steps) la.emb = nullptr;
             prof_begin(p, EBRL_K_OTHER);
             action_logits(la, p->stream);
             prof_end(p, 0, (double)c.n_bins * c.d * p->esz);

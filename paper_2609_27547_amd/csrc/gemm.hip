@@ -16,7 +16,8 @@
 //  * gemm_bf16_kernel: register-staged LDS tiles for the remaining shapes
 //    (K not a multiple of 64), with split-K partials reduced in split order
 //    by splitk_reduce_kernel.
-// fp32 path (fp32 policies): LDS-tiled FMA kernel with the same epilogues.
+// fp32 path (fp32 policies): fp32 MFMA on fragments from global memory, one
+// launch per product, with the same epilogues.
 // Every choice that orders a sum -- the K split count -- is a function of
 // (N, K) alone (plus M >= 256 for the large-M kernel); tile shapes, slice
 // widths and block order, which may follow M and the stream's CU count,
@@ -1105,81 +1106,121 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
 
 
 // ------------------------------------------------------------ fp32 GEMM --
-// 64 x 64 tile, BK 16, 256 threads; thread (ty, tx) owns rows 2ty, 2ty+1 and
-// columns grp*32 + q*4 + {0..3} and the same +16 (tx = grp*4 + q), so that a
-// SwiGLU gate/up pair is in one thread.
-template <bool PAIRED, bool SPLIT, class Epi>
+// (16 TM) x (16 TN) tiles on v_mfma_f32_16x16x4_f32 (fp32 products and sums),
+// fragments loaded straight from global memory: lane (r, g) holds four
+// consecutive K elements of row r, and MFMA step e takes element e of every
+// lane, so one 16-byte load per fragment row feeds four steps.  The four waves
+// take a quarter of K each and their tiles are summed in wave order through
+// LDS: an element's order is a function of K alone.  The fp32 policies are
+// small (launch latency, not bytes): splitting K inside the workgroup keeps
+// the load chain short and a product is one launch -- the 64 x 64 LDS tiles
+// it replaces took 24-91 us per prefill projection and 12.6 + 4.6 us (K split
+// over workgroups, then a reduction launch) per decode projection of the tiny
+// policy, where this takes 3-7.
+// NORM: output rows scaled by the RMSNorm factor of the input rows.
+template <int TM, int TN, bool NORM, bool PAIRED, class Epi>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda,
-                                                       const float* __restrict__ B, int ldb, int M,
-                                                       int N, int K, int k_per_split,
-                                                       float* __restrict__ ws, Epi epi)
+                                                       const float* __restrict__ B, int ldb, int M, int N,
+                                                       int K, float norm_eps, Epi epi)
 {
-    constexpr int TBM = 64, TBN = 64, TBK = 16;
-    __shared__ float sA[TBK][TBM + 4];
-    __shared__ float sB[TBK][TBN + 4];
-    const int tid = threadIdx.x;
-    const int tiles_n = (N + TBN - 1) / TBN;
+    constexpr int FR = TM * TN, G = PAIRED ? 2 : 1;
+    static_assert(!PAIRED || TN % 2 == 0, "paired epilogue needs fragment pairs");
+    constexpr int U = FR > 4 ? 2 : 4;   // 16-wide K groups loaded at a time
+    // operand rows need the alignment of a float only
+    typedef f32x4 f32x4_u __attribute__((aligned(4)));
+    __shared__ f32x4 red[4][FR * 64];
+    __shared__ float s_ssq[4][NORM ? TM * 16 : 1];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int tiles_n = (N + 16 * TN - 1) / (16 * TN);
     const int tmi = blockIdx.x / tiles_n, tni = blockIdx.x - tmi * tiles_n;
-    const int m0 = tmi * TBM, n0 = tni * TBN;
-    const int k_begin = blockIdx.y * k_per_split;
-    const int k_end = min(K, k_begin + k_per_split);
-    const int ty = tid >> 3, tx = tid & 7;
-    const int grp = tx >> 2, q = tx & 3;
-    int cols[8];
+    const int m0 = tmi * 16 * TM, n0 = tni * 16 * TN;
+    const int groups = (K + 15) >> 4, gpw = (groups + 3) >> 2;
+    const int g_begin = min(groups, wave * gpw), g_end = min(groups, g_begin + gpw);
+    const float* pa[TM];
+    const float* pb[TN];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        cols[c] = grp * 32 + q * 4 + c;
-        cols[4 + c] = grp * 32 + 16 + q * 4 + c;
+    for (int i = 0; i < TM; ++i) pa[i] = A + (size_t)min(m0 + i * 16 + r, M - 1) * lda + 4 * g;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) pb[j] = B + (size_t)min(n0 + j * 16 + r, N - 1) * ldb + 4 * g;
+    f32x4 acc[TM][TN];
+    float ssq[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        ssq[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    float acc[2][8];
+    for (int gi = g_begin; gi < g_end; gi += U) {
+        f32x4 a[U][TM], b[U][TN];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int u = 0; u < U; ++u) {
+            const int k = (gi + u) * 16;
+            // past the wave's range (K % 4 == 0): loaded from inside the row
+            // and zeroed, so that no load hangs on a branch
+            const bool in = gi + u < g_end && k + 4 * g < K;
+            const int off = min(k, K - 4 - 4 * g);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[i][c] = 0.f;
-
-    for (int k0 = k_begin; k0 < k_end; k0 += TBK) {
-        // 64 x 16 elements of A and of B: 4 per thread each
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            int e = tid + 256 * i;
-            int row = e >> 4, kk = e & 15;
-            int gk = k0 + kk;
-            float va = 0.f, vb = 0.f;
-            if (gk < k_end) {
-                va = A[(size_t)min(m0 + row, M - 1) * lda + gk];
-                vb = B[(size_t)min(n0 + row, N - 1) * ldb + gk];
+            for (int i = 0; i < TM; ++i) {
+                a[u][i] = *reinterpret_cast<const f32x4_u*>(pa[i] + off);
+                if (!in) a[u][i] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
-            sA[kk][row] = va;
-            sB[kk][row] = vb;
-        }
-        __syncthreads();
 #pragma unroll
-        for (int kk = 0; kk < TBK; ++kk) {
-            float a0 = sA[kk][2 * ty], a1 = sA[kk][2 * ty + 1];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                float b = sB[kk][cols[c]];
-                acc[0][c] = fmaf(a0, b, acc[0][c]);
-                acc[1][c] = fmaf(a1, b, acc[1][c]);
+            for (int j = 0; j < TN; ++j) {
+                b[u][j] = *reinterpret_cast<const f32x4_u*>(pb[j] + off);
+                if (!in) b[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    if constexpr (NORM) ssq[i] = fmaf(a[u][i][e], a[u][i][e], ssq[i]);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][j][e], a[u][i][e], acc[i][j], 0, 0, 0);
+                }
+        }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int m = m0 + 2 * ty + i;
-        if (m >= M) continue;
+    for (int i = 0; i < TM; ++i) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int n = n0 + cols[4 * h];
-            if (n >= N) continue;
-            float* v = &acc[i][4 * h];
-            if constexpr (SPLIT) {
-                st4<float>(ws + ((size_t)blockIdx.y * M + m) * N + n, v[0], v[1], v[2], v[3]);
-            } else if constexpr (PAIRED) {
-                if (h == 0) epi.pair(m, n, &acc[i][0], &acc[i][4]);
+        for (int j = 0; j < TN; ++j) red[wave][(i * TN + j) * 64 + lane] = acc[i][j];
+        if constexpr (NORM) {
+            float t = ssq[i];
+            t += __shfl_xor(t, 16, 64);
+            t += __shfl_xor(t, 32, 64);
+            if (g == 0) s_ssq[wave][i * 16 + r] = t;
+        }
+    }
+    __syncthreads();
+    for (int u = tid; u < FR / G * 64; u += 256) {
+        const int f0 = (u >> 6) * G, l = u & 63;
+        const int i = f0 / TN, j = f0 - i * TN;
+        const int m = m0 + i * 16 + (l & 15), n = n0 + j * 16 + 4 * (l >> 4);
+        f32x4 v[G];
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+            const int e = (f0 + h) * 64 + l;
+            v[h] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
+        }
+        if constexpr (NORM) {
+            const int row = i * 16 + (l & 15);
+            const float ss = ((s_ssq[0][row] + s_ssq[1][row]) + s_ssq[2][row]) + s_ssq[3][row];
+            const float rs = 1.0f / sqrtf(ss / (float)K + norm_eps);
+#pragma unroll
+            for (int h = 0; h < G; ++h) v[h] *= rs;
+        }
+        if (m < M && n < N) {
+            if constexpr (PAIRED) {
+                float gv[4] = {v[0][0], v[0][1], v[0][2], v[0][3]};
+                float uv[4] = {v[1][0], v[1][1], v[1][2], v[1][3]};
+                epi.pair(m, n, gv, uv);
             } else {
-                epi(m, n, v[0], v[1], v[2], v[3]);
+                epi(m, n, v[0][0], v[0][1], v[0][2], v[0][3]);
             }
         }
     }
@@ -1327,8 +1368,7 @@ static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool
         plan_in_order(p, M, N, K, cus);
         return p;
     }
-    if (!bf16) p.bm = 64;
-    else if (M <= 16) p.bm = 16;
+    if (M <= 16) p.bm = 16;
     else if (M <= 32) p.bm = 32;
     else if (M <= 64) p.bm = 64;
     else p.bm = 128;
@@ -1440,22 +1480,27 @@ static void launch_bf16(const GemmArgs& a, const GemmPlan& p, Epi epi, hipStream
 }
 
 template <bool PAIRED, class Epi>
-static void launch_f32(const GemmArgs& a, const GemmPlan& p, Epi epi, hipStream_t s) {
-    dim3 grid(((a.M + 63) / 64) * ((a.N + 63) / 64), p.splits);
-    if (p.splits > 1) {
-        hipLaunchKernelGGL((gemm_f32_kernel<PAIRED, true, Epi>), grid, dim3(256), 0, s,
-                           (const float*)a.A, a.lda, (const float*)a.B, a.ldb, a.M, a.N, a.K,
-                           p.k_per_split, a.ws, epi);
-        const int groups = PAIRED ? a.N / 8 : a.N / 4;
-        long total = (long)a.M * groups;
-        int blocks = (int)std::min<long>((total + 255) / 256, 4096);
-        hipLaunchKernelGGL((splitk_reduce_kernel<PAIRED, Epi>), dim3(blocks), dim3(256), 0, s,
-                           a.ws, p.splits, a.M, a.N, epi);
-    } else {
-        hipLaunchKernelGGL((gemm_f32_kernel<PAIRED, false, Epi>), grid, dim3(256), 0, s,
-                           (const float*)a.A, a.lda, (const float*)a.B, a.ldb, a.M, a.N, a.K,
-                           p.k_per_split, a.ws, epi);
+static void launch_f32(const GemmArgs& a, Epi epi, hipStream_t s) {
+    auto tiles = [&](int tm, int tn) {
+        return (long)((a.M + 16 * tm - 1) / (16 * tm)) * ((a.N + 16 * tn - 1) / (16 * tn));
+    };
+    auto go = [&](auto kern, int tm, int tn) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)tiles(tm, tn)), dim3(256), 0, s, (const float*)a.A, a.lda,
+                           (const float*)a.B, a.ldb, a.M, a.N, a.K, a.norm_eps, epi);
+    };
+    // The largest tile that still gives every CU two workgroups (64 x 64) or
+    // one (32 x 32); below that, latency counts and the smallest fragments win.
+    auto pick = [&](auto NORM) {
+        constexpr bool NM = decltype(NORM)::value;
+        if (a.M > 32 && tiles(4, 4) >= 512) go(gemm_f32_kernel<4, 4, NM, PAIRED, Epi>, 4, 4);
+        else if (a.M > 16 && tiles(2, 2) >= 256) go(gemm_f32_kernel<2, 2, NM, PAIRED, Epi>, 2, 2);
+        else if constexpr (PAIRED) go(gemm_f32_kernel<1, 2, NM, PAIRED, Epi>, 1, 2);
+        else go(gemm_f32_kernel<1, 1, NM, PAIRED, Epi>, 1, 1);
+    };
+    if constexpr (PAIRED) {
+        if (a.row_norm) { pick(std::true_type{}); return; }
     }
+    pick(std::false_type{});
 }
 
 template <bool PAIRED, class Epi>
@@ -1464,7 +1509,7 @@ static int dispatch(const GemmArgs& a, Epi epi, hipStream_t s) {
                                  a.split_ok && a.M <= SPLIT_MAX_M && (!a.bf16 || a.counters),
                                  std::max(1, std::min(a.cus, 256)));
     if (a.bf16) launch_bf16<PAIRED>(a, p, epi, s);
-    else launch_f32<PAIRED>(a, p, epi, s);
+    else launch_f32<PAIRED>(a, epi, s);
     return p.splits;
 }
 
@@ -1499,7 +1544,8 @@ int gemm_splits(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok)
 }
 
 bool gemm_row_norm_ok(bool bf16, int M, int N, int K, size_t ws_floats) {
-    if (!bf16 || M > SPLIT_MAX_M || K % 64) return false;
+    if (!bf16) return true;   // one workgroup always sees the whole K
+    if (M > SPLIT_MAX_M || K % 64) return false;
     const GemmPlan p = plan_gemm(true, M, N, K, ws_floats, true);
     return p.dec && p.splits == 1;
 }
@@ -1508,6 +1554,9 @@ size_t gemm_counter_words() {
     return DEC_MAX_COUNTERS;
 }
 
+// fp32 products write no partial sums; the count of the plan that once split
+// them is kept as what ebrl_op_gemm_noalloc accepts, so that no shape changes
+// sides.
 size_t gemm_ws_floats_used(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok) {
     const GemmPlan p = plan_gemm(bf16, M, N, K, ws_floats, split_ok && M <= SPLIT_MAX_M);
     if (p.splits <= 1) return 0;

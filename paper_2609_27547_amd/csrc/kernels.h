@@ -40,10 +40,11 @@ struct GemmArgs {
     // variant sums K in the same 64-wide steps, so results do not depend on M
     // either.
     bool split_ok = false;
-    // Decode GEMMs with a paired epilogue (EPI_QKV, EPI_SWIGLU) and one K
-    // split (gemm_row_norm_ok): A holds un-normalised rows in bf16 and every
-    // output row is scaled by 1/sqrt(mean_k A[m][k]^2 + norm_eps), i.e. the
-    // unit-gain RMSNorm of the input folded into the projection.
+    // GEMMs with a paired epilogue (EPI_QKV, EPI_SWIGLU) that gemm_row_norm_ok
+    // allows (bf16 decode with one K split; all fp32): A holds un-normalised
+    // rows and every output row is scaled by 1/sqrt(mean_k A[m][k]^2 +
+    // norm_eps), i.e. the unit-gain RMSNorm of the input folded into the
+    // projection.
     bool row_norm = false; float norm_eps = 1e-6f;
     // EPI_RESID: also store the updated rows in bf16 here (nullable).
     void* xb = nullptr; int ldxb = 0;
@@ -142,19 +143,17 @@ struct RopeKVArgs {
     bool use_rope = true;
 };
 
-// X[dst] = E[id] as float (id = ids[src ? src[i] : i*stride + off]; dst = dst_rows ? dst_rows[i] : i);
-// ids outside [0, n_rows_e) give zero rows.
-// xb (nullable, bf16 policies): the same rows in bf16 as well.
-void embed_rows(bool bf16, const void* E, int n_rows_e, int d, const int* ids, const int* src, int stride,
-                int off, const int* dst_rows, float* X, int ldx, int n, hipStream_t s, void* xb = nullptr,
-                int ldxb = 0);
+// X[dst_rows[i]] = E[ids[src[i]]] as float; ids outside [0, n_rows_e) give zero rows.
+void embed_rows(bool bf16, const void* E, int n_rows_e, int d, const int* ids, const int* src, const int* dst_rows,
+                float* X, int ldx, int n, hipStream_t s);
 
 // images f32 [n, cams, H, W, 3] -> patches [n*cams*(H/P)*(W/P), kpad] (zero-padded columns)
 void im2col(bool bf16, const float* img, int n, int cams, int H, int W, int P, void* out,
             int kpad, hipStream_t s);
 
 // Action head: logits = W_act . rmsnorm(x_row), argmax (ties -> lowest), top-2 margin,
-// bin -> action.  Writes column `col` of [n, ntok] outputs.
+// bin -> action.  Writes column `col` of [n, ntok] outputs and, with `emb`, the
+// chosen tokens' embedding rows as the next step's input rows 0 .. n - 1.
 struct LogitsArgs {
     bool bf16 = true;
     const float* X = nullptr; int ldx = 0;
@@ -164,8 +163,10 @@ struct LogitsArgs {
     float eps = 1e-6f;
     int* tokens = nullptr; float* actions = nullptr; float* margins = nullptr;
     int ntok = 7, col = 0;
-    // bf16 heads with d % 512 == 0 and n_bins % 64 == 0: logits scratch
-    // [n][n_bins] and n zeroed per-row counters (left zero after the call)
+    const void* emb = nullptr;      // [n_bins, d]
+    float* nx = nullptr; int ldnx = 0;   // next input rows
+    void* nxb = nullptr; int ldnxb = 0;  // the same in bf16 (nullable)
+    // logits scratch [n][n_bins] and n zeroed counters (left zero after the call)
     float* lg = nullptr; unsigned* counters = nullptr;
 };
 void action_logits(const LogitsArgs& a, hipStream_t s);

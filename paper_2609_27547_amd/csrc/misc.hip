@@ -113,38 +113,28 @@ void rmsnorm_rows(bool bf16_out, const float* X, int ldx, const int* rows, void*
 // ------------------------------------------------------------ embedding --
 template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(const T* E, int n_rows_e, int d, const int* ids,
-                                                    const int* src, int stride, int off, const int* dst_rows,
-                                                    float* X, int ldx, bf16_t* xb, int ldxb)
+                                                    const int* src, const int* dst_rows, float* X, int ldx)
 {
     const int i = blockIdx.x;
-    const int id = ids[src ? src[i] : i * stride + off];
-    const int dst = dst_rows ? dst_rows[i] : i;
-    float* x = X + (size_t)dst * ldx;
-    bf16_t* y = xb ? xb + (size_t)dst * ldxb : nullptr;
+    const int id = ids[src[i]];
+    float* x = X + (size_t)dst_rows[i] * ldx;
     if (id < 0 || id >= n_rows_e) {  // out-of-range ids embed as zero rows
-        for (int j = threadIdx.x; j < d; j += blockDim.x) {
-            x[j] = 0.f;
-            if (y) y[j] = 0;
-        }
+        for (int j = threadIdx.x; j < d; j += blockDim.x) x[j] = 0.f;
         return;
     }
     const T* e = E + (size_t)id * d;
-    for (int j = threadIdx.x; j < d; j += blockDim.x) {
-        const float v = ld_elem<T>(e + j);
-        x[j] = v;
-        if (y) st_elem<bf16_t>(y + j, v);
-    }
+    for (int j = threadIdx.x; j < d; j += blockDim.x) x[j] = ld_elem<T>(e + j);
 }
 
-void embed_rows(bool bf16, const void* E, int n_rows_e, int d, const int* ids, const int* src, int stride,
-                int off, const int* dst_rows, float* X, int ldx, int n, hipStream_t s, void* xb, int ldxb) {
+void embed_rows(bool bf16, const void* E, int n_rows_e, int d, const int* ids, const int* src, const int* dst_rows,
+                float* X, int ldx, int n, hipStream_t s) {
     if (n <= 0) return;
     if (bf16)
-        hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(n), dim3(256), 0, s, (const bf16_t*)E, n_rows_e, d,
-                           ids, src, stride, off, dst_rows, X, ldx, (bf16_t*)xb, ldxb);
+        hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(n), dim3(256), 0, s, (const bf16_t*)E, n_rows_e, d, ids, src,
+                           dst_rows, X, ldx);
     else
-        hipLaunchKernelGGL(embed_kernel<float>, dim3(n), dim3(256), 0, s, (const float*)E, n_rows_e, d,
-                           ids, src, stride, off, dst_rows, X, ldx, (bf16_t*)nullptr, 0);
+        hipLaunchKernelGGL(embed_kernel<float>, dim3(n), dim3(256), 0, s, (const float*)E, n_rows_e, d, ids, src,
+                           dst_rows, X, ldx);
 }
 
 // ----------------------------------------------------------- patchify --
@@ -193,147 +183,162 @@ void im2col(bool bf16, const float* img, int n, int cams, int H, int W, int P, v
 }
 
 // --------------------------------------------------------- action head --
-template <typename TW>
+// Grid (groups of RG rows, n_bins / (4 BPW)).  Each wave takes BPW bins for RG
+// rows: per 64 VEC columns one 16-byte piece of each bin's weight row and of
+// each input row per lane, every weight used RG times and every input BPW
+// times from registers; the rows' sums of squares come from the same loads and
+// scale the logits at the end, so nothing waits for a normalised copy of the
+// row.  The logits go to a scratch row, and the last of the row group's
+// workgroups (device-scope counter) takes each row's argmax (ties to the
+// lowest bin) and top-2 margin, one wave per row, and writes the token's
+// embedding as the next step's input row.  Latency bounds it: a workgroup per
+// (row, 64 bins) that first normalised its row into LDS took 17 us at 32 rows
+// of 4096 and 23 us at 104, and the embedding launch after it 7-10 us.
+template <typename TW, int RG>
 __global__ __launch_bounds__(256) void logits_kernel(LogitsArgs a)
 {
-    extern __shared__ float sh[];
-    float* hn = sh;              // [d]
-    float* lg = sh + a.d;        // [n_bins]
-    __shared__ float red[16];
-    const int i = blockIdx.x;
-    const int src = a.rows ? a.rows[i] : i;
-    const float* x = a.X + (size_t)src * a.ldx;
-    const float rs = row_rstd(x, a.d, a.eps, red);
-    for (int j = threadIdx.x; j < a.d; j += blockDim.x) hn[j] = x[j] * rs;
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    const TW* W = (const TW*)a.W;
-    for (int b = wave; b < a.n_bins; b += nw) {
-        float dot = 0.f;
-        for (int j = lane * 8; j < a.d; j += 512) {
-            float w[8];
-            load8v<TW>(W + (size_t)b * a.d + j, w);
+    constexpr int VEC = 16 / sizeof(TW);   // weights per lane and load
+    constexpr int BPW = 4;
+    __shared__ int s_last;
+    const int i0 = blockIdx.x * RG;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b0 = (blockIdx.y * 4 + wave) * BPW;
+    const TW* w[BPW];   // bins past the last repeat it
 #pragma unroll
-            for (int u = 0; u < 8; ++u) dot = fmaf(w[u], hn[j + u], dot);
-        }
-        dot = wave_sum(dot);
-        if (lane == 0) lg[b] = dot;
+    for (int b = 0; b < BPW; ++b) w[b] = (const TW*)a.W + (size_t)min(b0 + b, a.n_bins - 1) * a.d;
+    const float* x[RG];
+#pragma unroll
+    for (int q = 0; q < RG; ++q) {
+        const int i = min(i0 + q, a.n - 1);
+        x[q] = a.X + (size_t)(a.rows ? a.rows[i] : i) * a.ldx;
     }
+    float acc[BPW][RG], ssq[RG];
+#pragma unroll
+    for (int q = 0; q < RG; ++q) {
+        ssq[q] = 0.f;
+#pragma unroll
+        for (int b = 0; b < BPW; ++b) acc[b][q] = 0.f;
+    }
+#pragma unroll 2
+    for (int c = 0; c < a.d; c += 64 * VEC) {
+        const int col = c + lane * VEC, at = min(col, a.d - VEC);   // d % VEC == 0
+        float wf[BPW][VEC], h[RG][VEC];
+#pragma unroll
+        for (int b = 0; b < BPW; ++b) {
+            if constexpr (VEC == 8) {
+                load8v<TW>(w[b] + at, wf[b]);
+            } else {
+                const float4 v = *reinterpret_cast<const float4*>(w[b] + at);
+                wf[b][0] = v.x; wf[b][1] = v.y; wf[b][2] = v.z; wf[b][3] = v.w;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < RG; ++q)
+#pragma unroll
+            for (int u = 0; u < VEC; u += 4) {
+                const float4 v = *reinterpret_cast<const float4*>(x[q] + at + u);
+                h[q][u] = v.x; h[q][u + 1] = v.y; h[q][u + 2] = v.z; h[q][u + 3] = v.w;
+            }
+        if (col >= a.d) {
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) {
+#pragma unroll
+                for (int b = 0; b < BPW; ++b) wf[b][u] = 0.f;
+#pragma unroll
+                for (int q = 0; q < RG; ++q) h[q][u] = 0.f;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < RG; ++q)
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) {
+                ssq[q] = fmaf(h[q][u], h[q][u], ssq[q]);
+#pragma unroll
+                for (int b = 0; b < BPW; ++b) acc[b][q] = fmaf(wf[b][u], h[q][u], acc[b][q]);
+            }
+    }
+    // lane b * RG + q keeps bin b0 + b's logit of row i0 + q
+    float mine = 0.f;
+#pragma unroll
+    for (int q = 0; q < RG; ++q) {
+        const float rs = 1.0f / sqrtf(wave_sum(ssq[q]) / (float)a.d + a.eps);
+#pragma unroll
+        for (int b = 0; b < BPW; ++b) {
+            const float v = wave_sum(acc[b][q]) * rs;
+            if (lane == b * RG + q) mine = v;
+        }
+    }
+    const __amdgpu_buffer_rsrc_t lgr = coherent_rsrc(a.lg + (size_t)i0 * a.n_bins);
+    {
+        const int q = lane % RG, b = b0 + lane / RG;
+        if (lane < BPW * RG && b < a.n_bins && i0 + q < a.n) st_coherent1(lgr, (q * a.n_bins + b) * 4, mine);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (wave == 0) {
-        // argmax, ties to the lowest index
-        float bv = -INFINITY;
+    if (threadIdx.x == 0)
+        s_last = __hip_atomic_fetch_add(a.counters + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                 (unsigned)(gridDim.y - 1);
+    __syncthreads();
+    if (!s_last) return;
+    if (threadIdx.x == 0)
+        __hip_atomic_store(a.counters + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int q = wave; q < RG; q += 4) {
+        const int i = i0 + q;
+        if (i >= a.n) break;
+        // per lane: its largest logit (lowest bin of equals) and the largest of its others
+        float bv = -INFINITY, sv = -INFINITY;
         int bi = 0x7fffffff;
         for (int b = lane; b < a.n_bins; b += 64) {
-            const float v = lg[b];
-            if (v > bv || (v == bv && b < bi)) { bv = v; bi = b; }
+            const float v = ld_coherent1(lgr, (q * a.n_bins + b) * 4);
+            if (v > bv || (v == bv && b < bi)) { sv = bv; bv = v; bi = b; }
+            else sv = fmaxf(sv, v);
         }
+        const float own = bv;
+        const int own_i = bi;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             const float ov = __shfl_xor(bv, off, 64);
             const int oi = __shfl_xor(bi, off, 64);
             if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
         }
-        float sv = -INFINITY;
-        for (int b = lane; b < a.n_bins; b += 64)
-            if (b != bi) sv = fmaxf(sv, lg[b]);
-        sv = wave_max(sv);
+        sv = wave_max(own_i == bi ? sv : own);
         if (lane == 0) {
             const int o = i * a.ntok + a.col;
             a.tokens[o] = bi;
             if (a.actions) a.actions[o] = -1.0f + (2.0f * (float)bi + 1.0f) / (float)a.n_bins;
             if (a.margins) a.margins[o] = bv - sv;
         }
-    }
-}
-
-// bf16 action head, split over bins: grid (row, n_bins / 64).  A workgroup
-// normalises its row (RMSNorm, gains 1) into LDS, each wave takes 16 bins and
-// loads their weight rows in one burst per 512 columns; the row's logits go
-// to a scratch row, and the last of the row's workgroups (device-scope
-// counter) takes the argmax (ties to the lowest bin) and the top-2 margin.
-__global__ __launch_bounds__(256) void logits_split_kernel(LogitsArgs a)
-{
-    extern __shared__ float hn[];   // [d]
-    __shared__ float red[16];
-    __shared__ int s_last;
-    const int i = blockIdx.x, part = blockIdx.y;
-    const int src = a.rows ? a.rows[i] : i;
-    const float* x = a.X + (size_t)src * a.ldx;
-    const float rs = row_rstd(x, a.d, a.eps, red);
-    for (int j = threadIdx.x; j < a.d; j += blockDim.x) hn[j] = x[j] * rs;
-    __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b0 = part * 64 + wave * 16;
-    const bf16_t* W = (const bf16_t*)a.W + (size_t)b0 * a.d + lane * 8;
-    float acc[16];
+        if (a.emb) {
+            // NaN logits leave no maximum: a zero row, as for any id past the bins
+            const bool ok = bi < a.n_bins;
+            const TW* e = (const TW*)a.emb + (size_t)(ok ? bi : 0) * a.d;
+            for (int j = lane * 4; j < a.d; j += 256) {
+                float v[4];
 #pragma unroll
-    for (int b = 0; b < 16; ++b) acc[b] = 0.f;
-    for (int c = 0; c < a.d; c += 512) {
-        uint4 w[16];
-#pragma unroll
-        for (int b = 0; b < 16; ++b) w[b] = *reinterpret_cast<const uint4*>(W + (size_t)b * a.d + c);
-        float h[8];
-        const float4 h0 = *reinterpret_cast<const float4*>(hn + c + lane * 8);
-        const float4 h1 = *reinterpret_cast<const float4*>(hn + c + lane * 8 + 4);
-        h[0] = h0.x; h[1] = h0.y; h[2] = h0.z; h[3] = h0.w; h[4] = h1.x; h[5] = h1.y; h[6] = h1.z; h[7] = h1.w;
-#pragma unroll
-        for (int b = 0; b < 16; ++b) {
-            float wf[8];
-            load8v<bf16_t>(reinterpret_cast<const bf16_t*>(&w[b]), wf);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc[b] = fmaf(wf[u], h[u], acc[b]);
+                for (int u = 0; u < 4; ++u) v[u] = ok ? ld_elem<TW>(e + j + u) : 0.f;
+                st4<float>(a.nx + (size_t)i * a.ldnx + j, v[0], v[1], v[2], v[3]);
+                if (a.nxb) st4<bf16_t>((bf16_t*)a.nxb + (size_t)i * a.ldnxb + j, v[0], v[1], v[2], v[3]);
+            }
         }
-    }
-    const __amdgpu_buffer_rsrc_t lgr = coherent_rsrc(a.lg + (size_t)i * a.n_bins);
-#pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        const float v = wave_sum(acc[b]);
-        if (lane == b) st_coherent1(lgr, (b0 + b) * 4, v);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0)
-        s_last = __hip_atomic_fetch_add(a.counters + i, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                 (unsigned)(gridDim.y - 1);
-    __syncthreads();
-    if (!s_last || wave != 0) return;
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-    for (int b = lane; b < a.n_bins; b += 64) {
-        const float v = ld_coherent1(lgr, b * 4);
-        if (v > bv || (v == bv && b < bi)) { bv = v; bi = b; }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(bv, off, 64);
-        const int oi = __shfl_xor(bi, off, 64);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-    }
-    float sv = -INFINITY;
-    for (int b = lane; b < a.n_bins; b += 64)
-        if (b != bi) sv = fmaxf(sv, ld_coherent1(lgr, b * 4));
-    sv = wave_max(sv);
-    if (lane == 0) {
-        const int o = i * a.ntok + a.col;
-        a.tokens[o] = bi;
-        if (a.actions) a.actions[o] = -1.0f + (2.0f * (float)bi + 1.0f) / (float)a.n_bins;
-        if (a.margins) a.margins[o] = bv - sv;
-        __hip_atomic_store(a.counters + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
 void action_logits(const LogitsArgs& a, hipStream_t s) {
     if (a.n <= 0) return;
-    if (a.bf16 && a.lg && a.counters && a.d % 512 == 0 && a.n_bins % 64 == 0) {
-        hipLaunchKernelGGL(logits_split_kernel, dim3(a.n, a.n_bins / 64), dim3(256),
-                           (size_t)a.d * sizeof(float), s, a);
-        return;
+    // Rows per workgroup: one while the rows alone are few (each then has
+    // n_bins / 16 workgroups of its own), four from 16 rows on (a weight read
+    // serves four rows).
+    auto go = [&](auto kern, int rg) {
+        hipLaunchKernelGGL(kern, dim3((a.n + rg - 1) / rg, (a.n_bins + 15) / 16), dim3(256), 0, s, a);
+    };
+    if (a.bf16) {
+        if (a.n <= 16) go(logits_kernel<bf16_t, 1>, 1);
+        else go(logits_kernel<bf16_t, 4>, 4);
+    } else {
+        if (a.n <= 16) go(logits_kernel<float, 1>, 1);
+        else go(logits_kernel<float, 4>, 4);
     }
-    const size_t shm = (size_t)(a.d + a.n_bins) * sizeof(float);
-    if (a.bf16) hipLaunchKernelGGL(logits_kernel<bf16_t>, dim3(a.n), dim3(256), shm, s, a);
-    else hipLaunchKernelGGL(logits_kernel<float>, dim3(a.n), dim3(256), shm, s, a);
 }
 
 // ---------------------------------------------------- last prefix row --

@@ -177,6 +177,48 @@ def test_in_order_gemm_tile_and_round_edges_exact(M_, N, K):
     assert torch.equal(C.cpu(), a @ b.T)
 
 
+@pytest.mark.parametrize("M_,N,K", [(1, 4, 8), (16, 32, 64), (17, 20, 24), (33, 68, 136), (300, 36, 1032),
+                                    (520, 1300, 72), (1500, 2052, 200)])
+def test_fp32_gemm_tile_edges_exact(M_, N, K):
+    """fp32 products of small integers (exact sums) on 16-, 32- and 64-row
+    tiles: ragged rows and columns, K ranges of the four waves empty, partial
+    and whole, and operands aligned to one float only."""
+    g = torch.Generator().manual_seed(M_ + N + K)
+    a = torch.randint(-3, 4, (M_, K), generator=g).float()
+    b = torch.randint(-3, 4, (N, K), generator=g).float()
+    for shift in (0, 1):
+        A = torch.empty(M_ * K + shift, device="cuda")[shift:].view(M_, K).copy_(a)
+        B = torch.empty(N * K + shift, device="cuda")[shift:].view(N, K).copy_(b)
+        C = torch.full((M_, N), float("nan"), device="cuda")
+        E.op_gemm(A, B, C)
+        assert torch.equal(C.cpu(), a @ b.T), shift
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("n_bins,d,n", [(10, 64, 3), (250, 192, 19)])
+def test_action_head_ragged_bins_rows_and_width(bf16, n_bins, d, n):
+    """The action head where bins, rows and columns fill its waves partly
+    (one and four rows per workgroup), against the oracle."""
+    cfg = M.Config("head", bf16=bf16, n_cams=0, img=0, patch=0, layers=1, d=d, q_heads=1, kv_heads=1, head_dim=64,
+                   mlp=64, vocab=64, n_lang=5, n_bins=n_bins, n_action_tokens=4)
+    pol = E.Policy(_ebrl_config(cfg, n, 5), seed=3)
+    ids = list(range(n))
+    lang = synth_inputs.lang_ids(7, ids, 5, cfg.vocab)
+    pol.prefill(ids, lang_ids=_dev(lang))
+    tok, act, mar = pol.decode_actions(ids)
+    tok, act, mar = tok.cpu().numpy(), act.cpu().numpy(), mar.cpu().numpy()
+    ref = M.Policy(cfg, seed=3)
+    tol = P.TOL_BF16 if bf16 else P.TOL_FP32
+    for i in ids:
+        r = ref.decode(ref.prefill(None, lang[i]), forced=tok[i, :-1])
+        P.check_tokens(tok[i], r, n_bins)
+        _check_margins(pol, ref, i, mar[i], r, tol)
+        assert np.allclose(act[i], M.detokenize(tok[i], n_bins), atol=1e-6)
+    one, _, m1 = pol.decode_actions([ids[-1]])
+    assert np.array_equal(one.cpu().numpy()[0], tok[-1]) and np.array_equal(m1.cpu().numpy()[0], mar[-1])
+    pol.close()
+
+
 # ------------------------------------------------------- resident weights --
 
 @pytest.mark.parametrize("preset", [1, 2])
