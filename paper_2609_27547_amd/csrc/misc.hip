@@ -183,68 +183,81 @@ void im2col(bool bf16, const float* img, int n, int cams, int H, int W, int P, v
 }
 
 // --------------------------------------------------------- action head --
-// Grid (groups of RG rows, n_bins / (4 BPW)).  Each wave takes BPW bins for RG
-// rows: per 64 VEC columns one 16-byte piece of each bin's weight row and of
-// each input row per lane, every weight used RG times and every input BPW
-// times from registers; the rows' sums of squares come from the same loads and
+// Grid (groups of RG rows, groups of 16 bins).  The four waves deal the
+// columns out in pieces of 64 VEC; a wave loads its piece of 16 weight rows and
+// RG input rows (every weight serves RG rows, every input 16 bins) with all
+// loads in flight, and its 16 RG sums are reduced across the lanes by halving
+// (lane swaps that leave every lane a quarter of the sums), then across the
+// waves in wave order.  The rows' sums of squares come from the same loads and
 // scale the logits at the end, so nothing waits for a normalised copy of the
 // row.  The logits go to a scratch row, and the last of the row group's
 // workgroups (device-scope counter) takes each row's argmax (ties to the
 // lowest bin) and top-2 margin, one wave per row, and writes the token's
-// embedding as the next step's input row.  Latency bounds it: a workgroup per
-// (row, 64 bins) that first normalised its row into LDS took 17 us at 32 rows
-// of 4096 and 23 us at 104, and the embedding launch after it 7-10 us.
-template <typename TW, int RG>
-__global__ __launch_bounds__(256) void logits_kernel(LogitsArgs a)
+// embedding as the next step's input row, all its loads issued together.
+// Latency bounds it (the weights come from HBM once a step): 32 rows of 4096
+// 20.0 -> 14.2 us and one row of 1024 9.4 -> 7.9 us against waves that walked all
+// columns for four bins each and read the embedding 256 columns at a time.  An
+// element's summation order depends on d alone.
+EBRL_DEV float sum_xor32(float a, float b) {   // lanes < 32: a's pair sums, others: b's
+    const auto s = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                    false, false);
+    return __builtin_bit_cast(float, (unsigned)s[0]) + __builtin_bit_cast(float, (unsigned)s[1]);
+}
+EBRL_DEV float sum_xor16(float a, float b) {   // even rows of 16 lanes: a's pair sums, odd rows: b's
+    const auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                    false, false);
+    return __builtin_bit_cast(float, (unsigned)s[0]) + __builtin_bit_cast(float, (unsigned)s[1]);
+}
+
+template <typename TW, int VEC> EBRL_DEV void load_vec(const TW* p, float (&o)[VEC]) {
+    if constexpr (VEC == 8) {
+        load8v<TW>(p, o);
+    } else if constexpr (sizeof(TW) == 4) {
+        const float4 v = *reinterpret_cast<const float4*>(p);
+        o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
+    } else {
+        const uint2 v = *reinterpret_cast<const uint2*>(p);
+        o[0] = __uint_as_float(v.x << 16); o[1] = __uint_as_float(v.x & 0xFFFF0000u);
+        o[2] = __uint_as_float(v.y << 16); o[3] = __uint_as_float(v.y & 0xFFFF0000u);
+    }
+}
+
+constexpr int LOGIT_BINS = 16;   // bins per workgroup
+template <typename TW, int VEC, int RG>
+__global__ __launch_bounds__(256, 2) void logits_kernel(LogitsArgs a)
 {
-    constexpr int VEC = 16 / sizeof(TW);   // weights per lane and load
-    constexpr int BPW = 4;
-    __shared__ int s_last;
-    const int i0 = blockIdx.x * RG;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b0 = (blockIdx.y * 4 + wave) * BPW;
-    const TW* w[BPW];   // bins past the last repeat it
+    constexpr int NB = LOGIT_BINS, NA = NB * RG;
+    __shared__ float s_acc[4][NA], s_ssq[4][RG];
+    __shared__ int s_last, s_tok[RG];
+    const int i0 = blockIdx.x * RG, b0 = blockIdx.y * NB;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const TW* w[NB];   // bins past the last repeat it
 #pragma unroll
-    for (int b = 0; b < BPW; ++b) w[b] = (const TW*)a.W + (size_t)min(b0 + b, a.n_bins - 1) * a.d;
+    for (int b = 0; b < NB; ++b) w[b] = (const TW*)a.W + (size_t)min(b0 + b, a.n_bins - 1) * a.d;
     const float* x[RG];
 #pragma unroll
     for (int q = 0; q < RG; ++q) {
         const int i = min(i0 + q, a.n - 1);
         x[q] = a.X + (size_t)(a.rows ? a.rows[i] : i) * a.ldx;
     }
-    float acc[BPW][RG], ssq[RG];
+    float acc[NA], ssq[RG];
 #pragma unroll
-    for (int q = 0; q < RG; ++q) {
-        ssq[q] = 0.f;
+    for (int q = 0; q < RG; ++q) ssq[q] = 0.f;
 #pragma unroll
-        for (int b = 0; b < BPW; ++b) acc[b][q] = 0.f;
-    }
-#pragma unroll 2
-    for (int c = 0; c < a.d; c += 64 * VEC) {
+    for (int k = 0; k < NA; ++k) acc[k] = 0.f;
+    for (int c = wave * 64 * VEC; c < a.d; c += 4 * 64 * VEC) {
         const int col = c + lane * VEC, at = min(col, a.d - VEC);   // d % VEC == 0
-        float wf[BPW][VEC], h[RG][VEC];
+        float wf[NB][VEC], h[RG][VEC];
 #pragma unroll
-        for (int b = 0; b < BPW; ++b) {
-            if constexpr (VEC == 8) {
-                load8v<TW>(w[b] + at, wf[b]);
-            } else {
-                const float4 v = *reinterpret_cast<const float4*>(w[b] + at);
-                wf[b][0] = v.x; wf[b][1] = v.y; wf[b][2] = v.z; wf[b][3] = v.w;
-            }
-        }
+        for (int b = 0; b < NB; ++b) load_vec<TW, VEC>(w[b] + at, wf[b]);
 #pragma unroll
-        for (int q = 0; q < RG; ++q)
-#pragma unroll
-            for (int u = 0; u < VEC; u += 4) {
-                const float4 v = *reinterpret_cast<const float4*>(x[q] + at + u);
-                h[q][u] = v.x; h[q][u + 1] = v.y; h[q][u + 2] = v.z; h[q][u + 3] = v.w;
-            }
+        for (int q = 0; q < RG; ++q) load_vec<float, VEC>(x[q] + at, h[q]);
         if (col >= a.d) {
 #pragma unroll
             for (int u = 0; u < VEC; ++u) {
 #pragma unroll
-                for (int b = 0; b < BPW; ++b) wf[b][u] = 0.f;
+                for (int b = 0; b < NB; ++b) wf[b][u] = 0.f;
 #pragma unroll
                 for (int q = 0; q < RG; ++q) h[q][u] = 0.f;
             }
@@ -255,42 +268,54 @@ __global__ __launch_bounds__(256) void logits_kernel(LogitsArgs a)
             for (int u = 0; u < VEC; ++u) {
                 ssq[q] = fmaf(h[q][u], h[q][u], ssq[q]);
 #pragma unroll
-                for (int b = 0; b < BPW; ++b) acc[b][q] = fmaf(wf[b][u], h[q][u], acc[b][q]);
+                for (int b = 0; b < NB; ++b) acc[b * RG + q] = fmaf(wf[b][u], h[q][u], acc[b * RG + q]);
             }
     }
-    // lane b * RG + q keeps bin b0 + b's logit of row i0 + q
-    float mine = 0.f;
+    // Row g of 16 lanes ends with the sums NA / 2 (g >> 1) + NA / 4 (g & 1) + i;
+    // its lane i writes the i-th.
+    {
+        float t[NA / 2];
 #pragma unroll
-    for (int q = 0; q < RG; ++q) {
-        const float rs = 1.0f / sqrtf(wave_sum(ssq[q]) / (float)a.d + a.eps);
+        for (int k = 0; k < NA / 2; ++k) t[k] = sum_xor32(acc[k], acc[k + NA / 2]);
+        const int r = lane & 15, g = lane >> 4;
+        float mine = 0.f;
 #pragma unroll
-        for (int b = 0; b < BPW; ++b) {
-            const float v = wave_sum(acc[b][q]) * rs;
-            if (lane == b * RG + q) mine = v;
+        for (int k = 0; k < NA / 4; ++k) {
+            const float v = sum_lanes16(sum_xor16(t[k], t[k + NA / 4]));
+            if (r == k) mine = v;
+        }
+        if (r < NA / 4) s_acc[wave][NA / 2 * (g >> 1) + NA / 4 * (g & 1) + r] = mine;
+#pragma unroll
+        for (int q = 0; q < RG; ++q) {
+            const float v = wave_sum(ssq[q]);
+            if (lane == 0) s_ssq[wave][q] = v;
         }
     }
+    __syncthreads();
     const __amdgpu_buffer_rsrc_t lgr = coherent_rsrc(a.lg + (size_t)i0 * a.n_bins);
-    {
-        const int q = lane % RG, b = b0 + lane / RG;
-        if (lane < BPW * RG && b < a.n_bins && i0 + q < a.n) st_coherent1(lgr, (q * a.n_bins + b) * 4, mine);
+    if (tid < NA) {
+        const int q = tid % RG, b = b0 + tid / RG;
+        const float ss = ((s_ssq[0][q] + s_ssq[1][q]) + s_ssq[2][q]) + s_ssq[3][q];
+        const float rs = 1.0f / sqrtf(ss / (float)a.d + a.eps);
+        const float v = ((s_acc[0][tid] + s_acc[1][tid]) + s_acc[2][tid]) + s_acc[3][tid];
+        if (b < a.n_bins && i0 + q < a.n) st_coherent1(lgr, (q * a.n_bins + b) * 4, v * rs);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0)
+    if (tid == 0)
         s_last = __hip_atomic_fetch_add(a.counters + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                  (unsigned)(gridDim.y - 1);
     __syncthreads();
     if (!s_last) return;
-    if (threadIdx.x == 0)
-        __hip_atomic_store(a.counters + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int q = wave; q < RG; q += 4) {
-        const int i = i0 + q;
-        if (i >= a.n) break;
+    if (tid == 0) __hip_atomic_store(a.counters + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (wave < RG && i0 + wave < a.n) {
+        const int i = i0 + wave;
         // per lane: its largest logit (lowest bin of equals) and the largest of its others
         float bv = -INFINITY, sv = -INFINITY;
         int bi = 0x7fffffff;
+#pragma unroll 4
         for (int b = lane; b < a.n_bins; b += 64) {
-            const float v = ld_coherent1(lgr, (q * a.n_bins + b) * 4);
+            const float v = ld_coherent1(lgr, (wave * a.n_bins + b) * 4);
             if (v > bv || (v == bv && b < bi)) { sv = bv; bv = v; bi = b; }
             else sv = fmaxf(sv, v);
         }
@@ -308,17 +333,34 @@ __global__ __launch_bounds__(256) void logits_kernel(LogitsArgs a)
             a.tokens[o] = bi;
             if (a.actions) a.actions[o] = -1.0f + (2.0f * (float)bi + 1.0f) / (float)a.n_bins;
             if (a.margins) a.margins[o] = bv - sv;
+            s_tok[wave] = bi;
         }
-        if (a.emb) {
-            // NaN logits leave no maximum: a zero row, as for any id past the bins
-            const bool ok = bi < a.n_bins;
-            const TW* e = (const TW*)a.emb + (size_t)(ok ? bi : 0) * a.d;
-            for (int j = lane * 4; j < a.d; j += 256) {
-                float v[4];
+    }
+    if (!a.emb) return;
+    __syncthreads();
+    for (int j = tid * 8; j < a.d; j += 2048) {   // d % 8 == 0
+        float v[RG][8];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = ok ? ld_elem<TW>(e + j + u) : 0.f;
-                st4<float>(a.nx + (size_t)i * a.ldnx + j, v[0], v[1], v[2], v[3]);
-                if (a.nxb) st4<bf16_t>((bf16_t*)a.nxb + (size_t)i * a.ldnxb + j, v[0], v[1], v[2], v[3]);
+        for (int q = 0; q < RG; ++q) {
+            const int bi = s_tok[min(q, a.n - 1 - i0)];
+            // NaN logits leave no maximum: a zero row, as for any id past the bins
+            const bool ok = (unsigned)bi < (unsigned)a.n_bins;
+            load8v<TW>((const TW*)a.emb + (size_t)(ok ? bi : 0) * a.d + j, v[q]);
+            if (!ok) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[q][u] = 0.f;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < RG; ++q) {
+            if (i0 + q >= a.n) break;
+            float* const o = a.nx + (size_t)(i0 + q) * a.ldnx + j;
+            st4<float>(o, v[q][0], v[q][1], v[q][2], v[q][3]);
+            st4<float>(o + 4, v[q][4], v[q][5], v[q][6], v[q][7]);
+            if (a.nxb) {
+                bf16_t* const ob = (bf16_t*)a.nxb + (size_t)(i0 + q) * a.ldnxb + j;
+                st4<bf16_t>(ob, v[q][0], v[q][1], v[q][2], v[q][3]);
+                st4<bf16_t>(ob + 4, v[q][4], v[q][5], v[q][6], v[q][7]);
             }
         }
     }
@@ -328,17 +370,19 @@ void action_logits(const LogitsArgs& a, hipStream_t s) {
     if (a.n <= 0) return;
     // Rows per workgroup: one while the rows alone are few (each then has
     // n_bins / 16 workgroups of its own), four from 16 rows on (a weight read
-    // serves four rows).
+    // serves four rows).  16-byte weight loads once a row gives all four waves
+    // such a piece, 8-byte ones below; d alone decides, as it orders the sums.
     auto go = [&](auto kern, int rg) {
-        hipLaunchKernelGGL(kern, dim3((a.n + rg - 1) / rg, (a.n_bins + 15) / 16), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(kern, dim3((a.n + rg - 1) / rg, (a.n_bins + LOGIT_BINS - 1) / LOGIT_BINS), dim3(256), 0, s,
+                           a);
     };
-    if (a.bf16) {
-        if (a.n <= 16) go(logits_kernel<bf16_t, 1>, 1);
-        else go(logits_kernel<bf16_t, 4>, 4);
-    } else {
-        if (a.n <= 16) go(logits_kernel<float, 1>, 1);
-        else go(logits_kernel<float, 4>, 4);
-    }
+    auto rows = [&](auto kern1, auto kern4) {
+        if (a.n <= 16) go(kern1, 1);
+        else go(kern4, 4);
+    };
+    if (!a.bf16) rows(logits_kernel<float, 4, 1>, logits_kernel<float, 4, 4>);
+    else if (a.d >= 2048) rows(logits_kernel<bf16_t, 8, 1>, logits_kernel<bf16_t, 8, 4>);
+    else rows(logits_kernel<bf16_t, 4, 1>, logits_kernel<bf16_t, 4, 4>);
 }
 
 // ---------------------------------------------------- last prefix row --

@@ -219,6 +219,16 @@ def test_action_head_ragged_bins_rows_and_width(bf16, n_bins, d, n):
     pol.close()
 
 
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("n_bins,d,n", [(70, 2112, 18), (16, 1088, 17)])
+def test_action_head_wide_rows_and_partial_row_groups(bf16, n_bins, d, n):
+    """Widths around those where the head's waves load 16-byte instead of
+    8-byte weight pieces (the last piece partly filled), bins past the last
+    group of 16 and a last row group of one or two rows, against the oracle;
+    a row alone (one row per workgroup) gives the same bits."""
+    test_action_head_ragged_bins_rows_and_width(bf16, n_bins, d, n)
+
+
 # ------------------------------------------------------- resident weights --
 
 @pytest.mark.parametrize("preset", [1, 2])
