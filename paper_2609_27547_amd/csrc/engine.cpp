@@ -692,14 +692,29 @@ int denoise(ebrl_policy* p, const int32_t* env_ids, int32_t n, const float* fnoi
             normal_noise(p->flow_f, n, F * c.frame_dim, md + o_env, md + o_calls, p->seed, EBRL_NOISE_STREAM_FRAMES,
                          p->stream);
         prof_end(p, 0, 0);
-        for (int k = 0; k < c.n_steps; ++k) {
-            const float* tv = p->tvec + (size_t)k * c.exp_d;
+        // step k's output head and Euler update and step k + 1's input
+        // projection are one launch
+        FlowStepArgs f;
+        f.bf16 = p->bf16; f.H = p->X; f.ldh = c.exp_d; f.d = c.exp_d; f.per_out = S; f.n_steps = (float)c.n_steps;
+        FlowMod& act = f.mod[0];
+        act.x = act.x_out = p->flow_x; act.w_in = p->w_ain; act.w_out = p->w_aout;
+        act.adim = c.adim; act.rows = arows; act.per_in = c.chunk; act.off = F;
+        if (F) {
+            FlowMod& fr = f.mod[1];
+            fr.x = fr.x_out = p->flow_f; fr.w_in = p->w_fin; fr.w_out = p->w_fout;
+            fr.adim = c.frame_dim; fr.rows = frows; fr.per_in = F; fr.off = 0;
+        }
+        auto ends = [&](int done, int next) {   // steps that end and begin here (-1, n_steps: none)
+            f.last = done >= 0;
+            f.first = next < c.n_steps;
+            f.mod[0].v_out = done == 0 ? p->flow_v0 : nullptr;
+            f.tvec = f.first ? p->tvec + (size_t)next * c.exp_d : nullptr;
             prof_begin(p, EBRL_K_OTHER);
-            if (F) flow_in(p->bf16, p->flow_f, frows, c.frame_dim, p->w_fin, tv, c.exp_d, p->X, c.exp_d, F, S, 0,
-                           p->stream);
-            flow_in(p->bf16, p->flow_x, arows, c.adim, p->w_ain, tv, c.exp_d, p->X, c.exp_d, c.chunk, S, F,
-                    p->stream);
+            flow_step(f, p->stream);
             prof_end(p, 0, 0);
+        };
+        ends(-1, 0);
+        for (int k = 0; k < c.n_steps; ++k) {
             for (int l = 0; l < c.exp_layers; ++l) {
                 BlockCall b;
                 b.R = p->X; b.rows = rows; b.sd = &p->exp; b.w = &p->L_exp[l]; b.kv = dec_kv(p, l);
@@ -718,12 +733,7 @@ int denoise(ebrl_policy* p, const int32_t* env_ids, int32_t n, const float* fnoi
                 int rc2 = run_block(p, b);
                 if (rc2) return rc2;
             }
-            prof_begin(p, EBRL_K_OTHER);
-            if (F) flow_out(p->bf16, p->X, c.exp_d, frows, c.exp_d, p->w_fout, c.frame_dim, 1e-6f, (float)c.n_steps,
-                            p->flow_f, nullptr, F, S, 0, p->stream);
-            flow_out(p->bf16, p->X, c.exp_d, arows, c.exp_d, p->w_aout, c.adim, 1e-6f, (float)c.n_steps, p->flow_x,
-                     k == 0 ? p->flow_v0 : nullptr, c.chunk, S, F, p->stream);
-            prof_end(p, 0, 0);
+            ends(k, k + 1);
         }
         return check_launch(p);
     };

@@ -182,14 +182,27 @@ void gather_last(const float* X, int ldx, const int* seq_env, const int* last_ro
 void small_linear(bool bf16, const float* in, int R, int K, const void* W, int N, float* out,
                   bool silu_input, hipStream_t s);
 
-// Flow-matching input projection (+ time vector) and output head + Euler
-// update of one denoised modality; its token r lives in row
-// (r / per_in) * per_out + off + r % per_in of H.
-void flow_in(bool bf16, const float* x, int rows, int adim, const void* W_ain, const float* tvec,
-             int d, float* H, int ldh, int per_in, int per_out, int off, hipStream_t s);
-void flow_out(bool bf16, const float* H, int ldh, int rows, int d, const void* W_aout, int adim,
-              float eps, float n_steps, float* x, float* v_out, int per_in, int per_out, int off,
-              hipStream_t s);
+// The expert's ends of a denoising step, for one or two modalities (rows = 0:
+// none): with `last`, the output head on H and the Euler update x_out = x - v /
+// n_steps; then, with `first`, the input projection of x (updated or not) plus
+// the time vector, written to H.  A modality's token r lives in row
+// (r / per_in) * per_out + off + r % per_in of H.  d % 16 == 0, adim <= 64.
+struct FlowMod {
+    const float* x = nullptr; float* x_out = nullptr;   // [rows, adim]; may be the same buffer
+    float* v_out = nullptr;                             // velocities (nullable)
+    const void* w_in = nullptr;                         // [d, adim]
+    const void* w_out = nullptr;                        // [adim, d]
+    int adim = 0, rows = 0, per_in = 1, off = 0;
+};
+struct FlowStepArgs {
+    bool bf16 = true, last = false, first = false;
+    FlowMod mod[2];
+    float* H = nullptr; int ldh = 0;
+    int d = 0, per_out = 0;
+    const float* tvec = nullptr;
+    float eps = 1e-6f, n_steps = 1.f;
+};
+void flow_step(const FlowStepArgs& a, hipStream_t s);
 
 // Element copy (device) with f32 -> f32.
 void copy_f32(const float* src, float* dst, size_t n, hipStream_t s);

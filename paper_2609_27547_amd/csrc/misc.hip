@@ -409,34 +409,48 @@ void gather_last(const float* X, int ldx, const int* seq_env, const int* last_ro
 }
 
 // ------------------------------------------------------- small linear --
-// One wave per output column n, for all R input rows: the lanes read W's row
-// n and each input row in coalesced 64-element strides, then sum across the
-// wave (a fixed butterfly).
+// One wave per output column n and SL_ROWS input rows (grid: columns x row
+// groups): the lanes read W's row n and the input rows four elements at a time
+// (K % 4 == 0), every weight used for all the rows, then sum across the wave (a
+// fixed butterfly).  One row after the other behind its own loads took 60 us
+// for the ten time embeddings of a 1024-wide expert (now 10).
+constexpr int SL_ROWS = 4;
 template <typename T>
 __global__ __launch_bounds__(256) void small_linear_kernel(const float* in, int R, int K, const T* W, int N,
                                                            float* out, int silu_input)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int n = blockIdx.x * 4 + wave;
+    const int n = blockIdx.x * 4 + wave, r0 = blockIdx.y * SL_ROWS;
     if (n >= N) return;
     const T* w = W + (size_t)n * K;
-    for (int r = 0; r < R; ++r) {
-        const float* x = in + (size_t)r * K;
-        float acc = 0.f;
-        for (int k = lane; k < K; k += 64) {
-            float v = x[k];
-            if (silu_input) v = v / (1.0f + expf(-v));
-            acc = fmaf(v, ld_elem<T>(w + k), acc);
-        }
-        acc = wave_sum(acc);
-        if (lane == 0) out[(size_t)r * N + n] = acc;
+    float acc[SL_ROWS];
+#pragma unroll
+    for (int r = 0; r < SL_ROWS; ++r) acc[r] = 0.f;
+#pragma unroll 4
+    for (int k = lane * 4; k < K; k += 256) {
+        float wv[4], xv[SL_ROWS][4];
+        load_vec<T, 4>(w + k, wv);
+#pragma unroll
+        for (int r = 0; r < SL_ROWS; ++r) load_vec<float, 4>(in + (size_t)min(r0 + r, R - 1) * K + k, xv[r]);
+#pragma unroll
+        for (int r = 0; r < SL_ROWS; ++r)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = xv[r][e];
+                acc[r] = fmaf(silu_input ? v / (1.0f + expf(-v)) : v, wv[e], acc[r]);
+            }
+    }
+#pragma unroll
+    for (int r = 0; r < SL_ROWS; ++r) {
+        const float v = wave_sum(acc[r]);
+        if (lane == 0 && r0 + r < R) out[(size_t)(r0 + r) * N + n] = v;
     }
 }
 
 void small_linear(bool bf16, const float* in, int R, int K, const void* W, int N, float* out,
                   bool silu_input, hipStream_t s) {
     if (R <= 0 || N <= 0) return;
-    const dim3 grid((N + 3) / 4);
+    const dim3 grid((N + 3) / 4, (R + SL_ROWS - 1) / SL_ROWS);
     if (bf16)
         hipLaunchKernelGGL(small_linear_kernel<bf16_t>, grid, dim3(256), 0, s, in, R, K, (const bf16_t*)W, N,
                            out, (int)silu_input);
@@ -455,205 +469,150 @@ EBRL_DEV size_t flow_row(int r, int per_in, int per_out, int off) {
     return (size_t)(r / per_in) * per_out + off + r % per_in;
 }
 
-// A workgroup projects FLOW_IN_ROWS tokens onto 256 of the d outputs (grid:
-// row blocks x output slices, so that even a few thousand tokens fill the
-// chip): the tokens' inputs sit in LDS, each thread keeps its output's
-// weight row in registers and runs four tokens at a time (independent FMA
-// chains).  Each output is summed over the input channels in channel order,
-// then the time embedding is added.
-constexpr int FLOW_IN_ROWS = 16;
-template <typename T, int AMAX>
-__global__ __launch_bounds__(256) void flow_in_kernel(const float* __restrict__ x, int rows, int adim,
-                                                      const T* __restrict__ W_ain, const float* __restrict__ tvec,
-                                                      int d, float* __restrict__ H, int ldh, int per_in,
-                                                      int per_out, int off)
+// The expert's ends of a denoising step, FLOW_ROWS tokens of one modality per
+// workgroup: output head and Euler update of the step that ends (`last`), then
+// input projection plus time vector of the step that begins (`first`), both on
+// v_mfma_f32_16x16x4_f32 (fp32 products and sums).  A token needs only itself
+// for both, so a step costs one launch for all modalities, where the four
+// launches it replaces (a scalar weight load per channel, a wave reduction per
+// output) took 78 us on the world action model at 37 envs and this takes 22;
+// 64 envs of the flow policy 22 -> 16 us.
+//  * Head: the eight waves split d; lane (r, g) holds four consecutive columns
+//    of row r, one 16-byte load per four MFMA steps, and the same loads give
+//    the rows' sums of squares, which scale the sums at the end.  The waves'
+//    sums are added in wave order: an element's order depends on d alone.
+//  * Input: the updated tokens wait in LDS; lane group g of MFMA step s takes
+//    channel NS g + s, so that a lane's weights are consecutive.  Channels past
+//    adim are zeros.
+constexpr int FLOW_ROWS = 16, FLOW_WAVES = 8;
+
+template <typename T, int NT>   // NT: 16-channel tiles that cover adim
+EBRL_DEV void flow_step_body(const FlowStepArgs& a, const FlowMod& m, int r0, float* s_red, float (*s_ssq)[FLOW_ROWS],
+                             float* s_x)
 {
-    static_assert(FLOW_IN_ROWS % 4 == 0, "four tokens per pass");
-    __shared__ float sx[FLOW_IN_ROWS * AMAX];
-    const int r0 = blockIdx.x * FLOW_IN_ROWS;
-    const int nr = min(FLOW_IN_ROWS, rows - r0);
-    for (int i = threadIdx.x; i < FLOW_IN_ROWS * AMAX; i += blockDim.x) {
-        const int q = i / AMAX, j = i - q * AMAX;
-        sx[i] = (q < nr && j < adim) ? x[(size_t)(r0 + q) * adim + j] : 0.f;
-    }
-    __syncthreads();
-    const int o = blockIdx.y * blockDim.x + threadIdx.x;
-    if (o >= d) return;
-    float w[AMAX];
+    constexpr int NS = 4 * NT;                   // MFMA steps of the input projection
+    constexpr int XLD = 16 * NT + 4;             // LDS row of the tokens
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int d = a.d, adim = m.adim, row = min(r0 + r, m.rows - 1);
+    float* const hrow = a.H + flow_row(row, m.per_in, a.per_out, m.off) * a.ldh;
+    const int groups = d >> 4, gpw = (groups + FLOW_WAVES - 1) / FLOW_WAVES;   // d % 16 == 0
+    const int t_begin = min(groups, wave * gpw), t_end = min(groups, t_begin + gpw);
+
+    if (a.last) {
+        const T* pw[NT];   // channels past the last repeat it
 #pragma unroll
-    for (int j = 0; j < AMAX; ++j) w[j] = j < adim ? ld_elem<T>(W_ain + (size_t)o * adim + j) : 0.f;
-    const float t = tvec[o];
-    for (int q0 = 0; q0 < nr; q0 += 4) {
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NT; ++j) pw[j] = (const T*)m.w_out + (size_t)min(j * 16 + r, adim - 1) * d + 4 * g;
+        f32x4 acc[NT];
+        float ssq = 0.f;
 #pragma unroll
-        for (int j = 0; j < AMAX; ++j) {
-            if (j < adim) {
+        for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int t = t_begin; t < t_end; ++t) {
+            float h[4], w[NT][4];
+            load_vec<float, 4>(hrow + t * 16 + 4 * g, h);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) acc[u] = fmaf(w[j], sx[(q0 + u) * AMAX + j], acc[u]);
+            for (int j = 0; j < NT; ++j) load_vec<T, 4>(pw[j] + t * 16, w[j]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                ssq = fmaf(h[e], h[e], ssq);
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][e], h[e], acc[j], 0, 0, 0);
             }
         }
+        f32x4* const red = reinterpret_cast<f32x4*>(s_red);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (q0 + u < nr) H[flow_row(r0 + q0 + u, per_in, per_out, off) * ldh + o] = acc[u] + t;
+        for (int j = 0; j < NT; ++j) red[(wave * NT + j) * 64 + lane] = acc[j];
+        ssq += __shfl_xor(ssq, 16, 64);
+        ssq += __shfl_xor(ssq, 32, 64);
+        if (g == 0) s_ssq[wave][r] = ssq;
+        __syncthreads();
+        if (tid < NT * 64) {
+            // lane (r, g) of tile j: row r, channels 16 j + 4 g ..
+            const int j = tid >> 6;
+            f32x4 v = red[j * 64 + lane];
+            float ss = s_ssq[0][r];
+#pragma unroll
+            for (int w = 1; w < FLOW_WAVES; ++w) {
+                v += red[(w * NT + j) * 64 + lane];
+                ss += s_ssq[w][r];
+            }
+            const float rs = 1.0f / sqrtf(ss / (float)d + a.eps);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int c = j * 16 + 4 * g + e;
+                float xn = 0.f;
+                if (c < adim) {
+                    const size_t at = (size_t)row * adim + c;
+                    const float vel = v[e] * rs;
+                    xn = m.x[at] - vel / a.n_steps;
+                    if (r0 + r < m.rows) {
+                        m.x_out[at] = xn;
+                        if (m.v_out) m.v_out[at] = vel;
+                    }
+                }
+                s_x[r * XLD + c] = xn;
+            }
+        }
+    } else {
+        for (int u = tid; u < FLOW_ROWS * 16 * NT; u += 64 * FLOW_WAVES) {
+            const int q = u / (16 * NT), c = u % (16 * NT);
+            s_x[q * XLD + c] = c < adim ? m.x[(size_t)min(r0 + q, m.rows - 1) * adim + c] : 0.f;
+        }
     }
-}
-
-void flow_in(bool bf16, const float* x, int rows, int adim, const void* W_ain, const float* tvec,
-             int d, float* H, int ldh, int per_in, int per_out, int off, hipStream_t s) {
-    if (rows <= 0) return;
-    const dim3 grid((rows + FLOW_IN_ROWS - 1) / FLOW_IN_ROWS, (d + 255) / 256);
-    auto go = [&](auto amax) {
-        constexpr int AM = decltype(amax)::value;
-        if (bf16)
-            hipLaunchKernelGGL((flow_in_kernel<bf16_t, AM>), grid, dim3(256), 0, s, x, rows, adim,
-                               (const bf16_t*)W_ain, tvec, d, H, ldh, per_in, per_out, off);
-        else
-            hipLaunchKernelGGL((flow_in_kernel<float, AM>), grid, dim3(256), 0, s, x, rows, adim,
-                               (const float*)W_ain, tvec, d, H, ldh, per_in, per_out, off);
-    };
-    if (adim <= 8) go(std::integral_constant<int, 8>{});
-    else if (adim <= 32) go(std::integral_constant<int, 32>{});
-    else go(std::integral_constant<int, 64>{});   // adim <= 64 (checked at policy creation)
+    if (!a.first) return;
+    __syncthreads();
+    f32x4 xv[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) xv[j] = *reinterpret_cast<const f32x4*>(s_x + r * XLD + g * NS + 4 * j);
+    const bool vec = (adim & 3) == 0;
+#pragma unroll 4
+    for (int t = t_begin; t < t_end; ++t) {
+        const T* const pw = (const T*)m.w_in + (size_t)(t * 16 + r) * adim;
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int c = g * NS + 4 * j;
+            float w[4];
+            if (vec) {
+                load_vec<T, 4>(pw + min(c, adim - 4), w);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = ld_elem<T>(pw + min(c + e, adim - 1));
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c + e < adim ? w[e] : 0.f, xv[j][e], acc, 0, 0, 0);
+        }
+        const float4 tv = *reinterpret_cast<const float4*>(a.tvec + t * 16 + 4 * g);
+        if (r0 + r < m.rows)
+            st4<float>(hrow + t * 16 + 4 * g, acc[0] + tv.x, acc[1] + tv.y, acc[2] + tv.z, acc[3] + tv.w);
+    }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void flow_out_kernel(const float* H, int ldh, int d, const T* W_aout,
-                                                       int adim, float eps, float n_steps, float* x,
-                                                       float* v_out, int per_in, int per_out, int off)
+__global__ __launch_bounds__(64 * FLOW_WAVES) void flow_step_kernel(FlowStepArgs a)
 {
-    extern __shared__ float sh[];
-    float* hn = sh;          // [d]
-    float* vv = sh + d;      // [adim]
-    __shared__ float red[16];
-    const int r = blockIdx.x;
-    const float* h = H + flow_row(r, per_in, per_out, off) * ldh;
-    const float rs = row_rstd(h, d, eps, red);
-    for (int j = threadIdx.x; j < d; j += blockDim.x) hn[j] = h[j] * rs;
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    for (int c = wave; c < adim; c += nw) {
-        float dot = 0.f;
-        for (int j = lane; j < d; j += 64) dot = fmaf(ld_elem<T>(W_aout + (size_t)c * d + j), hn[j], dot);
-        dot = wave_sum(dot);
-        if (lane == 0) vv[c] = dot;
-    }
-    __syncthreads();
-    for (int c = threadIdx.x; c < adim; c += blockDim.x) {
-        const float v = vv[c];
-        x[(size_t)r * adim + c] -= v / n_steps;
-        if (v_out) v_out[(size_t)r * adim + c] = v;
-    }
+    constexpr int MAX_NT = 4;   // 64 channels (checked at policy creation)
+    __shared__ __attribute__((aligned(16))) float s_red[FLOW_WAVES * MAX_NT * 256];
+    __shared__ float s_ssq[FLOW_WAVES][FLOW_ROWS];
+    __shared__ __attribute__((aligned(16))) float s_x[FLOW_ROWS * (16 * MAX_NT + 4)];
+    const int blocks0 = (a.mod[0].rows + FLOW_ROWS - 1) / FLOW_ROWS;
+    const bool second = (int)blockIdx.x >= blocks0;
+    const FlowMod& m = a.mod[second ? 1 : 0];
+    const int r0 = ((int)blockIdx.x - (second ? blocks0 : 0)) * FLOW_ROWS;
+    if (m.adim <= 16) flow_step_body<T, 1>(a, m, r0, s_red, s_ssq, s_x);
+    else if (m.adim <= 32) flow_step_body<T, 2>(a, m, r0, s_red, s_ssq, s_x);
+    else flow_step_body<T, 4>(a, m, r0, s_red, s_ssq, s_x);
 }
 
-// The same projection with RW rows per wave (four waves per workgroup):
-// each lane holds columns 256 i + 4 lane .. + 3 of its rows in registers, a
-// weight row is loaded once for all of them, and every dot product and
-// sum of squares is summed per lane in column order, then over the lanes
-// (wave_sum).  For d a multiple of 256 up to 2048.
-template <typename T, int D4, int RW>
-__global__ __launch_bounds__(256) void flow_out_rows_kernel(const float* __restrict__ H, int ldh, int d,
-                                                            const T* __restrict__ W_aout, int adim, float eps,
-                                                            float n_steps, float* __restrict__ x,
-                                                            float* __restrict__ v_out, int rows, int per_in,
-                                                            int per_out, int off)
-{
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int r0 = (blockIdx.x * 4 + wave) * RW;
-    float4 hv[RW][D4];
-#pragma unroll
-    for (int k = 0; k < RW; ++k) {
-        float ss = 0.f;
-        if (r0 + k < rows) {
-            const float* h = H + flow_row(r0 + k, per_in, per_out, off) * ldh + 4 * lane;
-#pragma unroll
-            for (int i = 0; i < D4; ++i) {
-                hv[k][i] = *reinterpret_cast<const float4*>(h + 256 * i);
-                ss = fmaf(hv[k][i].x, hv[k][i].x, ss);
-                ss = fmaf(hv[k][i].y, hv[k][i].y, ss);
-                ss = fmaf(hv[k][i].z, hv[k][i].z, ss);
-                ss = fmaf(hv[k][i].w, hv[k][i].w, ss);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < D4; ++i) hv[k][i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        ss = wave_sum(ss);
-        const float rs = 1.0f / sqrtf(ss / (float)d + eps);
-#pragma unroll
-        for (int i = 0; i < D4; ++i) {
-            hv[k][i].x *= rs; hv[k][i].y *= rs; hv[k][i].z *= rs; hv[k][i].w *= rs;
-        }
-    }
-    float mine[RW];
-#pragma unroll
-    for (int k = 0; k < RW; ++k) mine[k] = 0.f;
-    for (int c = 0; c < adim; ++c) {
-        const T* wr = W_aout + (size_t)c * d + 4 * lane;
-        float acc[RW];
-#pragma unroll
-        for (int k = 0; k < RW; ++k) acc[k] = 0.f;
-#pragma unroll
-        for (int i = 0; i < D4; ++i) {
-            float w[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = ld_elem<T>(wr + 256 * i + e);
-#pragma unroll
-            for (int k = 0; k < RW; ++k) {
-                acc[k] = fmaf(w[0], hv[k][i].x, acc[k]);
-                acc[k] = fmaf(w[1], hv[k][i].y, acc[k]);
-                acc[k] = fmaf(w[2], hv[k][i].z, acc[k]);
-                acc[k] = fmaf(w[3], hv[k][i].w, acc[k]);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < RW; ++k) {
-            const float v = wave_sum(acc[k]);
-            if (lane == c) mine[k] = v;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < RW; ++k) {
-        const int r = r0 + k;
-        if (r < rows && lane < adim) {
-            x[(size_t)r * adim + lane] -= mine[k] / n_steps;
-            if (v_out) v_out[(size_t)r * adim + lane] = mine[k];
-        }
-    }
-}
-
-void flow_out(bool bf16, const float* H, int ldh, int rows, int d, const void* W_aout, int adim,
-              float eps, float n_steps, float* x, float* v_out, int per_in, int per_out, int off,
-              hipStream_t s) {
-    if (rows <= 0) return;
-    auto go = [&](auto d4, auto rw) {
-        constexpr int D4 = decltype(d4)::value, RW = decltype(rw)::value;
-        const dim3 grid((rows + 4 * RW - 1) / (4 * RW));
-        if (bf16)
-            hipLaunchKernelGGL((flow_out_rows_kernel<bf16_t, D4, RW>), grid, dim3(256), 0, s, H, ldh, d,
-                               (const bf16_t*)W_aout, adim, eps, n_steps, x, v_out, rows, per_in, per_out, off);
-        else
-            hipLaunchKernelGGL((flow_out_rows_kernel<float, D4, RW>), grid, dim3(256), 0, s, H, ldh, d,
-                               (const float*)W_aout, adim, eps, n_steps, x, v_out, rows, per_in, per_out, off);
-    };
-    using std::integral_constant;
-    if (d % 256 == 0 && adim <= 64) {
-        switch (d / 256) {
-        case 1: go(integral_constant<int, 1>{}, integral_constant<int, 4>{}); return;
-        case 2: go(integral_constant<int, 2>{}, integral_constant<int, 4>{}); return;
-        case 3: go(integral_constant<int, 3>{}, integral_constant<int, 4>{}); return;
-        case 4: go(integral_constant<int, 4>{}, integral_constant<int, 4>{}); return;
-        case 6: go(integral_constant<int, 6>{}, integral_constant<int, 2>{}); return;
-        case 8: go(integral_constant<int, 8>{}, integral_constant<int, 2>{}); return;
-        default: break;
-        }
-    }
-    const size_t shm = (size_t)(d + adim) * sizeof(float);
-    if (bf16)
-        hipLaunchKernelGGL(flow_out_kernel<bf16_t>, dim3(rows), dim3(256), shm, s, H, ldh, d,
-                           (const bf16_t*)W_aout, adim, eps, n_steps, x, v_out, per_in, per_out, off);
-    else
-        hipLaunchKernelGGL(flow_out_kernel<float>, dim3(rows), dim3(256), shm, s, H, ldh, d,
-                           (const float*)W_aout, adim, eps, n_steps, x, v_out, per_in, per_out, off);
+void flow_step(const FlowStepArgs& a, hipStream_t s) {
+    const int blocks = (a.mod[0].rows + FLOW_ROWS - 1) / FLOW_ROWS + (a.mod[1].rows + FLOW_ROWS - 1) / FLOW_ROWS;
+    if (blocks <= 0) return;
+    if (a.bf16) hipLaunchKernelGGL(flow_step_kernel<bf16_t>, dim3(blocks), dim3(64 * FLOW_WAVES), 0, s, a);
+    else hipLaunchKernelGGL(flow_step_kernel<float>, dim3(blocks), dim3(64 * FLOW_WAVES), 0, s, a);
 }
 
 __global__ void copy_f32_kernel(const float* src, float* dst, size_t n) {

@@ -647,6 +647,31 @@ def test_tiny_wam_bf16_parity_and_closed_forms(exp_d):
 
 
 
+@pytest.mark.parametrize("exp_d,adim,frame_dim", [(192, 4, 33), (64, 40, 64), (320, 17, 1)])
+def test_denoise_step_ends_channels_and_widths(exp_d, adim, frame_dim):
+    """The denoising steps' output head, Euler update and input projection at
+    one, two and four 16-channel tiles, vector and scalar weight loads, widths
+    that leave waves without columns and a last token block partly filled,
+    against the oracle."""
+    o = dataclasses.replace(TINY_WAM, exp_d=exp_d, adim=adim, frame_dim=frame_dim, chunk=9, frame_tokens=11, n_steps=3)
+    ids = [0, 2, 3]
+    img, lang = _obs(o, ids, 1005)
+    nf = synth_inputs.flow_noise(5, ids, o.frame_tokens, o.frame_dim)
+    na = synth_inputs.flow_noise(6, ids, o.chunk, o.adim)
+    pol = E.Policy(_ebrl_config(o, 4), seed=0)
+    pol.prefill(ids, images=_dev(img), lang_ids=_dev(lang))
+    f, a = pol.wam_denoise(ids, _dev(nf), _dev(na))
+    torch.cuda.synchronize()
+    f, a = f.cpu().numpy(), a.cpu().numpy()
+    ref = M.Policy(o, seed=0)
+    for i, e in enumerate(ids):
+        xf, xa, v0 = ref.wam_denoise(ref.prefill(img[i], lang[i]), nf[i], na[i], return_v0=True)
+        assert P.row_rel_err(pol.read_state(E.STATE_FLOW_V0, e), v0) < P.TOL_BF16
+        assert P.row_rel_err(f[i], xf) < P.TOL_BF16
+        assert P.row_rel_err(a[i], xa) < P.TOL_BF16
+    pol.close()
+
+
 @pytest.mark.parametrize("model", ["flow", "wam"])
 def test_denoise_batch_invariance_bitwise(model):
     """An env's denoised action chunk (and frames) do not depend on the call:
