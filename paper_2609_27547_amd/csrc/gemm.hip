@@ -298,6 +298,14 @@ template <int N> EBRL_DEV void wait_vmcnt() {
 }
 EBRL_DEV void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
+// Waits until at most min(later, MAX) groups of PER loads each are in flight.
+template <int MAX, int PER> EBRL_DEV void wait_tiles(int later) {
+    if constexpr (MAX > 0) {
+        if (later < MAX) { wait_tiles<MAX - 1, PER>(later); return; }
+    }
+    wait_vmcnt<MAX * PER>();
+}
+
 // Workgroup barrier without the waits of __syncthreads: the kernels below
 // count their own loads.  Neither memory accesses nor MFMAs move across it.
 EBRL_DEV void wg_barrier() {
@@ -774,8 +782,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
 // four waves split that range and run independent pipelines: each wave
 // streams its weight and activation rows into its own LDS region with
 // global_load_lds_dwordx4 (one instruction = 8 rows x 128 contiguous bytes,
-// whole cache lines), three buffers deep for 64-column slices where they fit
-// the LDS (two otherwise), and multiplies from LDS.  Loading
+// whole cache lines), two to four buffers deep, and multiplies from LDS.  Loading
 // whole 128-byte row segments per instruction roughly doubles the rate a CU
 // sustains compared with loading 16 rows x 64 bytes straight into MFMA
 // register layout.  The waves' tiles are summed in wave order through LDS.
@@ -820,31 +827,23 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
     constexpr int WE = BN * 64;            // bf16 per wave per buffer: weights
     constexpr int XE = TM * 16 * 64;       //                             activations
     constexpr int NDMA = (BN + TM * 16) / 8;       // DMA instructions per K group
-    // Three buffers per wave (two K groups in flight while a third is
-    // multiplied) for 64-column slices where they fit the LDS, else two:
-    // measured 1-13 % more bandwidth on the 7B-class decode shapes at 1-32
-    // rows; 32-column slices (small weights, launch-latency bound) lost
-    // up to 9 % from the larger LDS footprint.
-    constexpr int STAGES = (BN == 64 && 3 * 4 * (WE + XE) * 2 <= 150 * 1024) ? 3 : 2;
-    // one __shared__ object per buffer and operand, so that the compiler can
-    // tell the buffer being read from the one the DMA is filling
-    __shared__ __attribute__((aligned(1024))) bf16_t sW0[4 * WE];
-    __shared__ __attribute__((aligned(1024))) bf16_t sX0[4 * XE];
-    __shared__ __attribute__((aligned(1024))) bf16_t sW1[4 * WE];
-    __shared__ __attribute__((aligned(1024))) bf16_t sX1[4 * XE];
-    __shared__ __attribute__((aligned(1024))) bf16_t sW2[STAGES == 3 ? 4 * WE : 1];
-    __shared__ __attribute__((aligned(1024))) bf16_t sX2[STAGES == 3 ? 4 * XE : 1];
-    // After the main loop (every DMA landed, a barrier passed) the staging
-    // buffers hold the waves' tiles for the reduction -- wave w's region in
-    // sW0, then sX0, then sW1, none straddling two buffers -- and sX1 holds
-    // the per-row sums of squares and the last-workgroup flag (96-column
-    // slices of 64 rows fill the whole 160 KB with the two stages).
+    // K groups per wave in LDS, all but the one being multiplied in flight:
+    // three for 64-column slices where they fit (measured 1-13 % more
+    // bandwidth than two on the 7B-class decode shapes at 1-32 rows), two for
+    // 96-column slices (all of the LDS at 64 rows).  32-column slices of up to
+    // 32 rows run one workgroup per CU and are held by latency, not bytes: four
+    // (one row, K 1024 to 4096: 6.2 -> 5.6 us and 7.2 -> 6.4 us against two); at 64
+    // rows three are slower than two (7.5 -> 8.1 us).
+    constexpr int STAGE = (WE + XE) * 2;   // bytes per wave and group
+    constexpr int STAGES = BN == 96 ? 2 : BN == 32 ? (TM <= 2 ? 4 : 2) : (3 * 4 * STAGE <= 150 * 1024 ? 3 : 2);
+    __shared__ __attribute__((aligned(1024))) char smem[4 * STAGES * STAGE];
+    // After the main loop (every DMA landed, a barrier passed) it holds the
+    // waves' tiles for the reduction, the per-row sums of squares and the
+    // last-workgroup flag.
     constexpr int RB = FR * 64 * 16;   // bytes of one wave's tile
-    constexpr int CW = (int)sizeof(sW0) / RB, CX = (int)sizeof(sX0) / RB;
-    static_assert(CW + CX + CW >= 4, "reduction buffer");
-    static_assert((NORM ? 4 * TM * 16 * 4 : 0) + 4 <= (int)sizeof(sX1), "row sums and flag");
-    float (*const s_ssq)[TM * 16] = reinterpret_cast<float (*)[TM * 16]>(sX1);
-    int* const s_last = reinterpret_cast<int*>(sX1) + 4 * TM * 16;
+    static_assert(4 * RB + (NORM ? 4 * TM * 16 * 4 : 0) + 4 <= (int)sizeof(smem), "reduction buffer");
+    float (*const s_ssq)[TM * 16] = reinterpret_cast<float (*)[TM * 16]>(smem + 4 * RB);
+    int* const s_last = reinterpret_cast<int*>(smem + 4 * RB) + (NORM ? 4 * TM * 16 : 0);
     // K-split partial tiles are DEC_TILE_FLOATS apart in the workspace: the
     // plan splits K only for kernels whose tile fits that stride.
     constexpr bool SPLITTABLE = FR * 64 * 4 <= DEC_TILE_FLOATS;
@@ -873,13 +872,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
     const int w_begin = min(s_end, s_begin + wave * gpw);
     const int w_end = min(s_end, w_begin + gpw);
 
-    bf16_t* const w0 = sW0 + wave * WE; bf16_t* const x0 = sX0 + wave * XE;
-    bf16_t* const w1 = sW1 + wave * WE; bf16_t* const x1 = sX1 + wave * XE;
-    bf16_t* const w2 = sW2 + (STAGES == 3 ? wave * WE : 0);
-    bf16_t* const x2 = sX2 + (STAGES == 3 ? wave * XE : 0);
-    auto dma = [&](int grp, bf16_t* wl, bf16_t* xl) {
-        dec_dma<BN, NTW>(W, ldw, n0, N, grp * 64, wl, lane);
-        dec_dma<TM * 16>(A, lda, m0, M, grp * 64, xl, lane);
+    // buffer b of this wave: BN weight rows, then 16 TM activation rows
+    auto buf = [&](int b) { return reinterpret_cast<bf16_t*>(smem + (wave * STAGES + b) * STAGE); };
+    auto dma = [&](int grp, int b) {
+        dec_dma<BN, NTW>(W, ldw, n0, N, grp * 64, buf(b), lane);
+        dec_dma<TM * 16>(A, lda, m0, M, grp * 64, buf(b) + WE, lane);
     };
 
     // Output units: one fragment lane (or a gate/up fragment pair) each.
@@ -942,57 +939,26 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u][j], xb[u][i], acc[i][j], 0, 0, 0);
     };
 
-    if constexpr (STAGES == 3) {
-        // group g sits in buffer (g - w_begin) % 3; multiplying it first puts
-        // group g + 2 in flight into the buffer group g - 1 has left
-        auto step = [&](int gi, const bf16_t* wc, const bf16_t* xc, bf16_t* wn, bf16_t* xn) {
-            if (gi + 2 < w_end) {
-                dma(gi + 2, wn, xn);
-                wait_vmcnt<2 * NDMA>();
-            } else if (gi + 1 < w_end) {
-                wait_vmcnt<NDMA>();
-            } else {
-                wait_vmcnt<0>();
-            }
-            compute(wc, xc);
-        };
-        if (w_begin < w_end) dma(w_begin, w0, x0);
-        if (w_begin + 1 < w_end) dma(w_begin + 1, w1, x1);
-        for (int gi = w_begin; gi < w_end; gi += 3) {
-            step(gi, w0, x0, w2, x2);
-            if (gi + 1 >= w_end) break;
-            step(gi + 1, w1, x1, w0, x0);
-            if (gi + 2 >= w_end) break;
-            step(gi + 2, w2, x2, w1, x1);
-        }
-    } else if (w_begin < w_end) {
-        dma(w_begin, w0, x0);
-        for (int gi = w_begin; gi < w_end; gi += 2) {
-            if (gi + 1 < w_end) {
-                dma(gi + 1, w1, x1);
-                wait_vmcnt<NDMA>();
-            } else {
-                wait_vmcnt<0>();
-            }
-            compute(w0, x0);
-            if (gi + 1 >= w_end) break;
-            if (gi + 2 < w_end) {
-                dma(gi + 2, w0, x0);
-                wait_vmcnt<NDMA>();
-            } else {
-                wait_vmcnt<0>();
-            }
-            compute(w1, x1);
+    // group w_begin + i sits in buffer i % STAGES; multiplying it first puts
+    // the group STAGES - 1 further on in flight, into the buffer that the
+    // group before it has left
+#pragma unroll
+    for (int i = 0; i < STAGES - 1; ++i)
+        if (w_begin + i < w_end) dma(w_begin + i, i);
+    for (int gi = w_begin; gi < w_end; gi += STAGES) {
+#pragma unroll
+        for (int i = 0; i < STAGES; ++i) {
+            if (gi + i >= w_end) break;
+            wait_lds();   // the buffer refilled next has been read
+            if (gi + i + STAGES - 1 < w_end) dma(gi + i + STAGES - 1, (i + STAGES - 1) % STAGES);
+            wait_tiles<STAGES - 1, NDMA>(w_end - 1 - gi - i);
+            compute(buf(i), buf(i) + WE);
         }
     }
 
     // waves' tiles through LDS (the staging buffers, once every wave is done)
     __syncthreads();
-    auto red_region = [&](int w) -> f32x4* {
-        if (w < CW) return reinterpret_cast<f32x4*>(sW0) + w * FR * 64;
-        if (w < CW + CX) return reinterpret_cast<f32x4*>(sX0) + (w - CW) * FR * 64;
-        return reinterpret_cast<f32x4*>(sW1) + (w - CW - CX) * FR * 64;
-    };
+    auto red_region = [&](int w) { return reinterpret_cast<f32x4*>(smem + w * RB); };
     f32x4* const red = red_region(wave);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
