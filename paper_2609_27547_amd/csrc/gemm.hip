@@ -1084,14 +1084,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
 // over workgroups, then a reduction launch) per decode projection of the tiny
 // policy, where this takes 3-7.
 // NORM: output rows scaled by the RMSNorm factor of the input rows.
-template <int TM, int TN, bool NORM, bool PAIRED, class Epi>
+// U: 16-wide K groups loaded at a time.
+template <int TM, int TN, int U, bool NORM, bool PAIRED, class Epi>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda,
                                                        const float* __restrict__ B, int ldb, int M, int N,
                                                        int K, float norm_eps, Epi epi)
 {
     constexpr int FR = TM * TN, G = PAIRED ? 2 : 1;
     static_assert(!PAIRED || TN % 2 == 0, "paired epilogue needs fragment pairs");
-    constexpr int U = FR > 4 ? 2 : 4;   // 16-wide K groups loaded at a time
     // operand rows need the alignment of a float only
     typedef f32x4 f32x4_u __attribute__((aligned(4)));
     __shared__ f32x4 red[4][FR * 64];
@@ -1458,10 +1458,14 @@ static void launch_f32(const GemmArgs& a, Epi epi, hipStream_t s) {
     // one (32 x 32); below that, latency counts and the smallest fragments win.
     auto pick = [&](auto NORM) {
         constexpr bool NM = decltype(NORM)::value;
-        if (a.M > 32 && tiles(4, 4) >= 512) go(gemm_f32_kernel<4, 4, NM, PAIRED, Epi>, 4, 4);
-        else if (a.M > 16 && tiles(2, 2) >= 256) go(gemm_f32_kernel<2, 2, NM, PAIRED, Epi>, 2, 2);
-        else if constexpr (PAIRED) go(gemm_f32_kernel<1, 2, NM, PAIRED, Epi>, 1, 2);
-        else go(gemm_f32_kernel<1, 1, NM, PAIRED, Epi>, 1, 1);
+        if (a.M > 32 && tiles(4, 4) >= 512) go(gemm_f32_kernel<4, 4, 2, NM, PAIRED, Epi>, 4, 4);
+        else if (a.M > 16 && tiles(2, 2) >= 256) go(gemm_f32_kernel<2, 2, 4, NM, PAIRED, Epi>, 2, 2);
+        else if constexpr (PAIRED) go(gemm_f32_kernel<1, 2, 4, NM, PAIRED, Epi>, 1, 2);
+        // Long K: a wave's quarter of it in rounds of 256 instead of 64 elements,
+        // each a memory latency (8 rows, K 1024: 8.1 -> 6.9 us, the tiny policy's call
+        // 438 -> 414 us); below, rounds of 256 would mostly load padding.
+        else if (a.K >= 1024) go(gemm_f32_kernel<1, 1, 16, NM, PAIRED, Epi>, 1, 1);
+        else go(gemm_f32_kernel<1, 1, 4, NM, PAIRED, Epi>, 1, 1);
     };
     if constexpr (PAIRED) {
         if (a.row_norm) { pick(std::true_type{}); return; }
