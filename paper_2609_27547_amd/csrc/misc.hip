@@ -26,6 +26,19 @@ template <> EBRL_DEV void load8v<float>(const float* p, float* o) {
     o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
 }
 
+template <typename TW, int VEC> EBRL_DEV void load_vec(const TW* p, float (&o)[VEC]) {
+    if constexpr (VEC == 8) {
+        load8v<TW>(p, o);
+    } else if constexpr (sizeof(TW) == 4) {
+        const float4 v = *reinterpret_cast<const float4*>(p);
+        o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
+    } else {
+        const uint2 v = *reinterpret_cast<const uint2*>(p);
+        o[0] = __uint_as_float(v.x << 16); o[1] = __uint_as_float(v.x & 0xFFFF0000u);
+        o[2] = __uint_as_float(v.y << 16); o[3] = __uint_as_float(v.y & 0xFFFF0000u);
+    }
+}
+
 // sum of squares of a row (fixed order), then 1/sqrt(mean + eps)
 EBRL_DEV float row_rstd(const float* x, int d, float eps, float* red) {
     float ss = 0.f;
@@ -118,12 +131,15 @@ __global__ __launch_bounds__(256) void embed_kernel(const T* E, int n_rows_e, in
     const int i = blockIdx.x;
     const int id = ids[src[i]];
     float* x = X + (size_t)dst_rows[i] * ldx;
-    if (id < 0 || id >= n_rows_e) {  // out-of-range ids embed as zero rows
-        for (int j = threadIdx.x; j < d; j += blockDim.x) x[j] = 0.f;
-        return;
+    // four elements a thread and access (d % 4 == 0), 16-byte stores: 7959 rows of
+    // 4096 55 -> 35 us against one element each
+    const bool ok = id >= 0 && id < n_rows_e;   // out-of-range ids embed as zero rows
+    const T* e = E + (size_t)(ok ? id : 0) * d;
+    for (int j = threadIdx.x * 4; j < d; j += blockDim.x * 4) {
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        if (ok) load_vec<T, 4>(e + j, v);
+        st4<float>(x + j, v[0], v[1], v[2], v[3]);
     }
-    const T* e = E + (size_t)id * d;
-    for (int j = threadIdx.x; j < d; j += blockDim.x) x[j] = ld_elem<T>(e + j);
 }
 
 void embed_rows(bool bf16, const void* E, int n_rows_e, int d, const int* ids, const int* src, const int* dst_rows,
@@ -207,19 +223,6 @@ EBRL_DEV float sum_xor16(float a, float b) {   // even rows of 16 lanes: a's pai
     const auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
                                                     false, false);
     return __builtin_bit_cast(float, (unsigned)s[0]) + __builtin_bit_cast(float, (unsigned)s[1]);
-}
-
-template <typename TW, int VEC> EBRL_DEV void load_vec(const TW* p, float (&o)[VEC]) {
-    if constexpr (VEC == 8) {
-        load8v<TW>(p, o);
-    } else if constexpr (sizeof(TW) == 4) {
-        const float4 v = *reinterpret_cast<const float4*>(p);
-        o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
-    } else {
-        const uint2 v = *reinterpret_cast<const uint2*>(p);
-        o[0] = __uint_as_float(v.x << 16); o[1] = __uint_as_float(v.x & 0xFFFF0000u);
-        o[2] = __uint_as_float(v.y << 16); o[3] = __uint_as_float(v.y & 0xFFFF0000u);
-    }
 }
 
 constexpr int LOGIT_BINS = 16;   // bins per workgroup
