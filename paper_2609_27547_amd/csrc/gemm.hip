@@ -1,14 +1,16 @@
 // Projections y = x W^T of every linear layer (W stored [out, in]).
 //
-// bf16 path, three kernels, all on v_mfma_f32_16x16x32_bf16 with fp32
+// bf16 path, four kernels, all on v_mfma_f32_16x16x32_bf16 with fp32
 // accumulation.  The weight tile feeds the MFMA "A" operand and the
 // activation tile the "B" operand, so a lane ends up owning four consecutive
 // output columns of one row: a SwiGLU gate/up pair lands in the same lane
 // (weights packed in 32-row groups: 16 gate rows, then the 16 matching up
 // rows), and so does a rotary pair of the fused QKV projection.
-//  * gemm_bf16_big_kernel (M >= 256: prefill, ViT, flow expert): 256 x 256,
-//    192 x 256 or 128 x 128 tiles (16, 12 or 8 waves), operands DMA'd
-//    global -> LDS, epilogue staged through LDS for whole-row stores.
+//  * gemm_bf16_big_kernel (prefill, ViT, experts): 256 x 256 tiles on two
+//    groups of four waves, operands DMA'd global -> LDS, epilogue staged
+//    through LDS for whole-row stores.
+//  * gemm_bf16_ring_kernel (the same, outputs with few such tiles): 64 x 128,
+//    64 x 64 or 32 x 64 tiles, K tiles in an LDS ring.
 //  * gemm_bf16_decode_kernel (decode, M <= 256): 32-, 64- or 96-column slices, per-wave
 //    LDS pipelines fed by whole-line DMA; K split across workgroups only for
 //    narrow outputs, the partials summed in split order inside the kernel by
@@ -19,7 +21,7 @@
 // fp32 path (fp32 policies): fp32 MFMA on fragments from global memory, one
 // launch per product, with the same epilogues.
 // Every choice that orders a sum -- the K split count -- is a function of
-// (N, K) alone (plus M >= 256 for the large-M kernel); tile shapes, slice
+// (N, K) alone; tile shapes, slice
 // widths and block order, which may follow M and the stream's CU count,
 // never change an element's summation order.  Results therefore do not
 // depend on timing, on the number of compute units or on how many rows a
