@@ -555,10 +555,7 @@ EBRL_DEV uint4 ld_stream16(const bf16_t* p) {
 
 template <int HD> constexpr int attn_decode_chunk() { return 65536 / HD; }
 
-// PRE: the next round's rows are loaded before the current one is worked on.
-// Twice the row registers halve the waves a CU holds: chosen where the grid
-// leaves them unused anyway (attn_decode).
-template <int HD, bool PRE>
+template <int HD>
 __global__ __launch_bounds__(256) void attn_decode_bf16_kernel(AttnDecodeArgs a, float scale_log2)
 {
     constexpr int LPK = HD / 8;        // lanes per key row, 16 bytes each
@@ -600,7 +597,8 @@ __global__ __launch_bounds__(256) void attn_decode_bf16_kernel(AttnDecodeArgs a,
     float m_run = -INFINITY, l_run = 0.f, acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-    auto load = [&](int kb, uint4 (&kr)[NL], uint4 (&vr)[NL]) {
+    for (int kb = wb; kb < we; kb += KW) {
+        uint4 kr[NL], vr[NL];
 #pragma unroll
         for (int t = 0; t < NL; ++t) {
             const int key = min(kb + t * KPL + kq, we - 1);
@@ -608,8 +606,6 @@ __global__ __launch_bounds__(256) void attn_decode_bf16_kernel(AttnDecodeArgs a,
             kr[t] = ld_stream16(kbase + off);
             vr[t] = ld_stream16(vbase + off);
         }
-    };
-    auto round = [&](int kb, const uint4 (&kr)[NL], const uint4 (&vr)[NL]) {
         float sc[NL];
         float mr = -INFINITY;
 #pragma unroll
@@ -639,25 +635,6 @@ __global__ __launch_bounds__(256) void attn_decode_bf16_kernel(AttnDecodeArgs a,
             for (int j = 0; j < 8; ++j) acc[j] = fmaf(p, vv[j], acc[j]);
         }
         m_run = m_new;
-    };
-    if constexpr (PRE) {
-        uint4 k0r[NL], v0r[NL], k1r[NL], v1r[NL];
-        if (wb < we) load(wb, k0r, v0r);
-        for (int kb = wb; kb < we; kb += 2 * KW) {
-            if (kb + KW < we) load(kb + KW, k1r, v1r);
-            __builtin_amdgcn_sched_barrier(0);
-            round(kb, k0r, v0r);
-            if (kb + KW >= we) break;
-            if (kb + 2 * KW < we) load(kb + 2 * KW, k0r, v0r);
-            __builtin_amdgcn_sched_barrier(0);
-            round(kb + KW, k1r, v1r);
-        }
-    } else {
-        for (int kb = wb; kb < we; kb += KW) {
-            uint4 kr[NL], vr[NL];
-            load(kb, kr, vr);
-            round(kb, kr, vr);
-        }
     }
     // lanes of one key slot hold the same l; sum over the key slots
     auto slots_sum = [&](float v) {
@@ -747,17 +724,15 @@ void attn_decode(const AttnDecodeArgs& a, hipStream_t s) {
     if (a.bf16) {
         // chunks of the longest sequence the part buffer is laid out for
         const int keys = a.max_splits * ATTN_DEC_CHUNK;
-        auto go = [&](auto plain, auto pre, int ck) {
-            const dim3 grid(a.n, a.q_heads, (keys + ck - 1) / ck);
-            // Prefetching pays up to one workgroup per CU (one env of 16 heads,
-            // 430 keys: 7.3 -> 6.85 us); beyond, it costs waves in flight (64
-            // such envs 20.2 -> 23.3 us; 32 envs of 32 heads of 128 27.2 -> 29.4 us).
-            // The order of the sums is the same.
-            if ((long)grid.x * grid.y * grid.z <= 256) hipLaunchKernelGGL(pre, grid, dim3(256), 0, s, a, scale_log2);
-            else hipLaunchKernelGGL(plain, grid, dim3(256), 0, s, a, scale_log2);
-        };
-        if (hd == 64) go(attn_decode_bf16_kernel<64, false>, attn_decode_bf16_kernel<64, true>, attn_decode_chunk<64>());
-        else go(attn_decode_bf16_kernel<128, false>, attn_decode_bf16_kernel<128, true>, attn_decode_chunk<128>());
+        if (hd == 64) {
+            constexpr int CK = attn_decode_chunk<64>();
+            hipLaunchKernelGGL(attn_decode_bf16_kernel<64>, dim3(a.n, a.q_heads, (keys + CK - 1) / CK), dim3(256), 0,
+                               s, a, scale_log2);
+        } else {
+            constexpr int CK = attn_decode_chunk<128>();
+            hipLaunchKernelGGL(attn_decode_bf16_kernel<128>, dim3(a.n, a.q_heads, (keys + CK - 1) / CK), dim3(256), 0,
+                               s, a, scale_log2);
+        }
     } else {
         if (hd == 64) {
             hipLaunchKernelGGL((attn_decode_split_kernel<float, 64>), g1, dim3(256), 0, s, a, scale_log2);
