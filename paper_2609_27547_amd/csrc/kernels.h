@@ -186,7 +186,7 @@ void small_linear(bool bf16, const float* in, int R, int K, const void* W, int N
 // none): with `last`, the output head on H and the Euler update x_out = x - v /
 // n_steps; then, with `first`, the input projection of x (updated or not) plus
 // the time vector, written to H.  A modality's token r lives in row
-// (r / per_in) * per_out + off + r % per_in of H.  d % 16 == 0, adim <= 64.
+// (r / per_in) * per_out + off + r % per_in of H.  d % 64 == 0, adim <= 64.
 struct FlowMod {
     const float* x = nullptr; float* x_out = nullptr;   // [rows, adim]; may be the same buffer
     float* v_out = nullptr;                             // velocities (nullable)

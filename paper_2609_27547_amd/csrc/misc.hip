@@ -39,12 +39,15 @@ template <typename TW, int VEC> EBRL_DEV void load_vec(const TW* p, float (&o)[V
     }
 }
 
+// four squares, the order that row sums of squares are fixed to
+EBRL_DEV float sq4(float4 v) { return fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.x, v.x, v.y * v.y))); }
+
 // sum of squares of a row (fixed order), then 1/sqrt(mean + eps)
 EBRL_DEV float row_rstd(const float* x, int d, float eps, float* red) {
     float ss = 0.f;
     for (int j = threadIdx.x * 4; j < d; j += blockDim.x * 4) {
         const float4 v = *reinterpret_cast<const float4*>(x + j);
-        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        ss += sq4(v);
     }
     ss = block_sum(ss, red);
     return 1.0f / sqrtf(ss / (float)d + eps);
@@ -413,10 +416,10 @@ void gather_last(const float* X, int ldx, const int* seq_env, const int* last_ro
 
 // ------------------------------------------------------- small linear --
 // One wave per output column n and SL_ROWS input rows (grid: columns x row
-// groups): the lanes read W's row n and the input rows four elements at a time
-// (K % 4 == 0), every weight used for all the rows, then sum across the wave (a
-// fixed butterfly).  One row after the other behind its own loads took 60 us
-// for the ten time embeddings of a 1024-wide expert (now 10).
+// groups): lane l sums columns l + 64 i of W's row n and of the input rows, every
+// weight used for all the rows, then the lanes are summed (wave_sum): that order
+// is fixed, as for the step ends below.  One row after the other behind its own
+// loads took 60 us for the ten time embeddings of a 1024-wide expert (now 11).
 constexpr int SL_ROWS = 4;
 template <typename T>
 __global__ __launch_bounds__(256) void small_linear_kernel(const float* in, int R, int K, const T* W, int N,
@@ -429,19 +432,17 @@ __global__ __launch_bounds__(256) void small_linear_kernel(const float* in, int 
     float acc[SL_ROWS];
 #pragma unroll
     for (int r = 0; r < SL_ROWS; ++r) acc[r] = 0.f;
-#pragma unroll 4
-    for (int k = lane * 4; k < K; k += 256) {
-        float wv[4], xv[SL_ROWS][4];
-        load_vec<T, 4>(w + k, wv);
+#pragma unroll 8
+    for (int k = lane; k < K; k += 64) {
+        const float wv = ld_elem<T>(w + k);
+        float xv[SL_ROWS];
 #pragma unroll
-        for (int r = 0; r < SL_ROWS; ++r) load_vec<float, 4>(in + (size_t)min(r0 + r, R - 1) * K + k, xv[r]);
+        for (int r = 0; r < SL_ROWS; ++r) xv[r] = in[(size_t)min(r0 + r, R - 1) * K + k];
 #pragma unroll
-        for (int r = 0; r < SL_ROWS; ++r)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float v = xv[r][e];
-                acc[r] = fmaf(silu_input ? v / (1.0f + expf(-v)) : v, wv[e], acc[r]);
-            }
+        for (int r = 0; r < SL_ROWS; ++r) {
+            const float v = xv[r];
+            acc[r] = fmaf(silu_input ? v / (1.0f + expf(-v)) : v, wv, acc[r]);
+        }
     }
 #pragma unroll
     for (int r = 0; r < SL_ROWS; ++r) {
@@ -474,86 +475,153 @@ EBRL_DEV size_t flow_row(int r, int per_in, int per_out, int off) {
 
 // The expert's ends of a denoising step, FLOW_ROWS tokens of one modality per
 // workgroup: output head and Euler update of the step that ends (`last`), then
-// input projection plus time vector of the step that begins (`first`), both on
-// v_mfma_f32_16x16x4_f32 (fp32 products and sums).  A token needs only itself
-// for both, so a step costs one launch for all modalities, where the four
-// launches it replaces (a scalar weight load per channel, a wave reduction per
-// output) took 78 us on the world action model at 37 envs and this takes 22;
-// 64 envs of the flow policy 22 -> 16 us.
-//  * Head: the eight waves split d; lane (r, g) holds four consecutive columns
-//    of row r, one 16-byte load per four MFMA steps, and the same loads give
-//    the rows' sums of squares, which scale the sums at the end.  The waves'
-//    sums are added in wave order: an element's order depends on d alone.
-//  * Input: the updated tokens wait in LDS; lane group g of MFMA step s takes
-//    channel NS g + s, so that a lane's weights are consecutive.  Channels past
-//    adim are zeros.
+// input projection plus time vector of the step that begins (`first`).  A token
+// needs only itself for both, so a step costs one launch for all modalities,
+// where a launch per modality and end (a scalar weight load per channel, a wave
+// reduction per output) took 78 us on the world action model at 37 envs and this
+// takes 28 (rows from and to memory: 45 MB, 8 us); 64 envs of the flow policy 18.
+//
+// These sums have one fixed order: a change of it passes through every bf16
+// layer that follows and ends as 4e-4 of the actions after ten steps.  (The
+// order that fits 16-byte loads and 16x16x4 MFMAs best, with the row factor
+// applied to the sums, took 25 us on the world action model.)  Both products run
+// on v_mfma_f32_16x16x1_4b_f32, whose four blocks each take one fma per element:
+// an accumulator is an fma chain.
+//  * Head: a normalised row h * rs has 64 partial sums: chains over columns
+//    256 i + 4 l + e (i, then e; l = 0 .. 63) where the width is 1, 2, 3, 4, 6 or 8
+//    times 256 (16-byte loads), over columns l + 64 i for other widths.  They are
+//    added as a balanced tree, neighbours first.  Block g of an MFMA is partial
+//    sum 4 u + g; a wave has eight of them (two u), so that it adds its own subtree
+//    of eight, and the waves' sums are the last three levels.  A row's sum of
+//    squares takes the same tree (other widths: row_rstd's with 256 threads).
+//    The row is read again after it, from the caches: kept in registers it would
+//    leave one workgroup a CU.
+//  * Input: chains over the channels; block g is output columns 16 g .. of 64,
+//    the updated tokens come from LDS.
 constexpr int FLOW_ROWS = 16, FLOW_WAVES = 8;
+
+// row_rstd's sum of squares (256 threads) by one wave
+EBRL_DEV float row_ssq_wave(const float* x, int d, int lane) {
+    float t = 0.f;
+    for (int v = 0; v < 4; ++v) {
+        float ss = 0.f;
+        for (int j = (v * 64 + lane) * 4; j < d; j += 1024) ss += sq4(*reinterpret_cast<const float4*>(x + j));
+        t += wave_sum(ss);
+    }
+    return t;
+}
 
 template <typename T, int NT>   // NT: 16-channel tiles that cover adim
 EBRL_DEV void flow_step_body(const FlowStepArgs& a, const FlowMod& m, int r0, float* s_red, float (*s_ssq)[FLOW_ROWS],
                              float* s_x)
 {
-    constexpr int NS = 4 * NT;                   // MFMA steps of the input projection
     constexpr int XLD = 16 * NT + 4;             // LDS row of the tokens
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int d = a.d, adim = m.adim, row = min(r0 + r, m.rows - 1);
     float* const hrow = a.H + flow_row(row, m.per_in, a.per_out, m.off) * a.ldh;
-    const int groups = d >> 4, gpw = (groups + FLOW_WAVES - 1) / FLOW_WAVES;   // d % 16 == 0
-    const int t_begin = min(groups, wave * gpw), t_end = min(groups, t_begin + gpw);
+    f32x16 zero;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) zero[i] = 0.f;
 
     if (a.last) {
         const T* pw[NT];   // channels past the last repeat it
 #pragma unroll
-        for (int j = 0; j < NT; ++j) pw[j] = (const T*)m.w_out + (size_t)min(j * 16 + r, adim - 1) * d + 4 * g;
-        f32x4 acc[NT];
-        float ssq = 0.f;
+        for (int j = 0; j < NT; ++j) pw[j] = (const T*)m.w_out + (size_t)min(j * 16 + r, adim - 1) * d;
+        // the wave's sums: lane (r, g) of tile j holds row r, channels 16 j + 4 g ..
+        f32x4* const red = reinterpret_cast<f32x4*>(s_red);
+        auto add_sums = [&](const f32x16 (&acc)[NT], int u) {
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < NT; ++j) {
+                // register 4 b + i of an accumulator: block b, channel 4 g + i, row r
+                f32x4 t;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t[i] = (acc[j][i] + acc[j][4 + i]) + (acc[j][8 + i] + acc[j][12 + i]);
+                f32x4& at = red[(wave * NT + j) * 64 + lane];
+                at = u ? at + t : t;
+            }
+        };
+        auto rstd = [&](float ss) { return 1.0f / sqrtf(ss / (float)d + a.eps); };
+        const int d4 = d >> 8;
+        if ((d & 255) == 0 && (d4 <= 4 || d4 == 6 || d4 == 8)) {
+            const int c0 = 32 * wave + 4 * g;   // columns of partial sum 8 wave + 4 u + g: c0 + 16 u ..
+            float ss[2] = {0.f, 0.f};
 #pragma unroll 4
-        for (int t = t_begin; t < t_end; ++t) {
-            float h[4], w[NT][4];
-            load_vec<float, 4>(hrow + t * 16 + 4 * g, h);
+            for (int i = 0; i < d4; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) load_vec<T, 4>(pw[j] + t * 16, w[j]);
+                for (int u = 0; u < 2; ++u) {
+                    float h[4];
+                    load_vec<float, 4>(hrow + 256 * i + c0 + 16 * u, h);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                ssq = fmaf(h[e], h[e], ssq);
+                    for (int e = 0; e < 4; ++e) ss[u] = fmaf(h[e], h[e], ss[u]);
+                }
 #pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][e], h[e], acc[j], 0, 0, 0);
+            for (int u = 0; u < 2; ++u) {
+                ss[u] += __shfl_xor(ss[u], 16, 64);
+                ss[u] += __shfl_xor(ss[u], 32, 64);
+            }
+            if (g == 0) s_ssq[wave][r] = ss[0] + ss[1];
+            __syncthreads();
+            const float rs = rstd(((s_ssq[0][r] + s_ssq[1][r]) + (s_ssq[2][r] + s_ssq[3][r])) +
+                                  ((s_ssq[4][r] + s_ssq[5][r]) + (s_ssq[6][r] + s_ssq[7][r])));
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                f32x16 acc[NT];
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[j] = zero;
+#pragma unroll 2
+                for (int i = 0; i < d4; ++i) {
+                    float h[4], w[NT][4];
+                    load_vec<float, 4>(hrow + 256 * i + c0 + 16 * u, h);
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) load_vec<T, 4>(pw[j] + 256 * i + c0 + 16 * u, w[j]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j)
+                            acc[j] = __builtin_amdgcn_mfma_f32_16x16x1f32(w[j][e], h[e] * rs, acc[j], 0, 0, 0);
+                }
+                add_sums(acc, u);
+            }
+        } else {
+            for (int q = wave; q < FLOW_ROWS; q += FLOW_WAVES) {
+                const int qr = min(r0 + q, m.rows - 1);
+                const float ss = row_ssq_wave(a.H + flow_row(qr, m.per_in, a.per_out, m.off) * a.ldh, d, lane);
+                if (lane == 0) s_ssq[0][q] = ss;
+            }
+            __syncthreads();
+            const float rs = rstd(s_ssq[0][r]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                f32x16 acc[NT];
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[j] = zero;
+#pragma unroll 2
+                for (int col = 8 * wave + 4 * u + g; col < d; col += 64) {   // d % 64 == 0
+                    const float x = hrow[col] * rs;
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x1f32(ld_elem<T>(pw[j] + col), x, acc[j], 0, 0, 0);
+                }
+                add_sums(acc, u);
             }
         }
-        f32x4* const red = reinterpret_cast<f32x4*>(s_red);
-#pragma unroll
-        for (int j = 0; j < NT; ++j) red[(wave * NT + j) * 64 + lane] = acc[j];
-        ssq += __shfl_xor(ssq, 16, 64);
-        ssq += __shfl_xor(ssq, 32, 64);
-        if (g == 0) s_ssq[wave][r] = ssq;
         __syncthreads();
         if (tid < NT * 64) {
-            // lane (r, g) of tile j: row r, channels 16 j + 4 g ..
             const int j = tid >> 6;
-            f32x4 v = red[j * 64 + lane];
-            float ss = s_ssq[0][r];
-#pragma unroll
-            for (int w = 1; w < FLOW_WAVES; ++w) {
-                v += red[(w * NT + j) * 64 + lane];
-                ss += s_ssq[w][r];
-            }
-            const float rs = 1.0f / sqrtf(ss / (float)d + a.eps);
+            auto of = [&](int w) { return red[(w * NT + j) * 64 + lane]; };
+            const f32x4 vel = ((of(0) + of(1)) + (of(2) + of(3))) + ((of(4) + of(5)) + (of(6) + of(7)));
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int c = j * 16 + 4 * g + e;
                 float xn = 0.f;
                 if (c < adim) {
                     const size_t at = (size_t)row * adim + c;
-                    const float vel = v[e] * rs;
-                    xn = m.x[at] - vel / a.n_steps;
+                    xn = m.x[at] - vel[e] / a.n_steps;
                     if (r0 + r < m.rows) {
                         m.x_out[at] = xn;
-                        if (m.v_out) m.v_out[at] = vel;
+                        if (m.v_out) m.v_out[at] = vel[e];
                     }
                 }
                 s_x[r * XLD + c] = xn;
@@ -567,38 +635,48 @@ EBRL_DEV void flow_step_body(const FlowStepArgs& a, const FlowMod& m, int r0, fl
     }
     if (!a.first) return;
     __syncthreads();
-    f32x4 xv[NT];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) xv[j] = *reinterpret_cast<const f32x4*>(s_x + r * XLD + g * NS + 4 * j);
     const bool vec = (adim & 3) == 0;
-#pragma unroll 4
-    for (int t = t_begin; t < t_end; ++t) {
-        const T* const pw = (const T*)m.w_in + (size_t)(t * 16 + r) * adim;
-        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = wave; t < d >> 6; t += FLOW_WAVES) {
+        const T* const pw_in = (const T*)m.w_in + (size_t)(t * 64 + lane) * adim;   // block g, column r of it
+        float w[4 * NT][4];   // channels past the last: zeros, which leave a sum as it is
+        if (vec) {
 #pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int c = g * NS + 4 * j;
-            float w[4];
-            if (vec) {
-                load_vec<T, 4>(pw + min(c, adim - 4), w);
-            } else {
+            for (int c = 0; c < 4 * NT; ++c) load_vec<T, 4>(pw_in + min(4 * c, adim - 4), w[c]);
+        } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = ld_elem<T>(pw + min(c + e, adim - 1));
-            }
+            for (int c = 0; c < 4 * NT; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c + e < adim ? w[e] : 0.f, xv[j][e], acc, 0, 0, 0);
+                for (int e = 0; e < 4; ++e) {
+                    w[c][e] = ld_elem<T>(pw_in + min(4 * c + e, adim - 1));
+                    if (4 * c + e >= adim) w[c][e] = 0.f;
+                }
         }
-        const float4 tv = *reinterpret_cast<const float4*>(a.tvec + t * 16 + 4 * g);
+        f32x16 acc = zero;
+#pragma unroll
+        for (int c = 0; c < 4 * NT; ++c) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(s_x + r * XLD + 4 * c);   // zeros past adim
+            if (4 * c < adim) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x1f32(w[c][e], x[e], acc, 0, 0, 0);
+            }
+        }
         if (r0 + r < m.rows)
-            st4<float>(hrow + t * 16 + 4 * g, acc[0] + tv.x, acc[1] + tv.y, acc[2] + tv.z, acc[3] + tv.w);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int col = t * 64 + 16 * b + 4 * g;
+                const float4 tv = *reinterpret_cast<const float4*>(a.tvec + col);
+                st4<float>(hrow + col, acc[4 * b] + tv.x, acc[4 * b + 1] + tv.y, acc[4 * b + 2] + tv.z,
+                           acc[4 * b + 3] + tv.w);
+            }
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(64 * FLOW_WAVES) void flow_step_kernel(FlowStepArgs a)
+// MAX_NT: tiles of the widest modality; up to 32 channels two workgroups fit a
+// CU's registers.
+template <typename T, int MAX_NT>
+__global__ __launch_bounds__(64 * FLOW_WAVES, MAX_NT <= 2 && sizeof(T) == 2 ? 4 : 2) void flow_step_kernel(FlowStepArgs a)
 {
-    constexpr int MAX_NT = 4;   // 64 channels (checked at policy creation)
     __shared__ __attribute__((aligned(16))) float s_red[FLOW_WAVES * MAX_NT * 256];
     __shared__ float s_ssq[FLOW_WAVES][FLOW_ROWS];
     __shared__ __attribute__((aligned(16))) float s_x[FLOW_ROWS * (16 * MAX_NT + 4)];
@@ -606,16 +684,19 @@ __global__ __launch_bounds__(64 * FLOW_WAVES) void flow_step_kernel(FlowStepArgs
     const bool second = (int)blockIdx.x >= blocks0;
     const FlowMod& m = a.mod[second ? 1 : 0];
     const int r0 = ((int)blockIdx.x - (second ? blocks0 : 0)) * FLOW_ROWS;
-    if (m.adim <= 16) flow_step_body<T, 1>(a, m, r0, s_red, s_ssq, s_x);
-    else if (m.adim <= 32) flow_step_body<T, 2>(a, m, r0, s_red, s_ssq, s_x);
-    else flow_step_body<T, 4>(a, m, r0, s_red, s_ssq, s_x);
+    if (MAX_NT == 1 || m.adim <= 16) flow_step_body<T, 1>(a, m, r0, s_red, s_ssq, s_x);
+    else if (MAX_NT == 2 || m.adim <= 32) flow_step_body<T, 2>(a, m, r0, s_red, s_ssq, s_x);
+    else flow_step_body<T, MAX_NT>(a, m, r0, s_red, s_ssq, s_x);
 }
 
 void flow_step(const FlowStepArgs& a, hipStream_t s) {
     const int blocks = (a.mod[0].rows + FLOW_ROWS - 1) / FLOW_ROWS + (a.mod[1].rows + FLOW_ROWS - 1) / FLOW_ROWS;
     if (blocks <= 0) return;
-    if (a.bf16) hipLaunchKernelGGL(flow_step_kernel<bf16_t>, dim3(blocks), dim3(64 * FLOW_WAVES), 0, s, a);
-    else hipLaunchKernelGGL(flow_step_kernel<float>, dim3(blocks), dim3(64 * FLOW_WAVES), 0, s, a);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * FLOW_WAVES), 0, s, a); };
+    const int wide = std::max(a.mod[0].adim, a.mod[1].adim);   // <= 64 (checked at policy creation)
+    if (wide <= 16) a.bf16 ? go(flow_step_kernel<bf16_t, 1>) : go(flow_step_kernel<float, 1>);
+    else if (wide <= 32) a.bf16 ? go(flow_step_kernel<bf16_t, 2>) : go(flow_step_kernel<float, 2>);
+    else a.bf16 ? go(flow_step_kernel<bf16_t, 4>) : go(flow_step_kernel<float, 4>);
 }
 
 __global__ void copy_f32_kernel(const float* src, float* dst, size_t n) {

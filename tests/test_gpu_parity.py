@@ -4,6 +4,7 @@ Inputs are the seeded synthetic observations of synth_inputs; expected
 values come only from the CPU oracle (oracle/).  Criteria in tests/parity.py.
 """
 import dataclasses
+import math
 
 import numpy as np
 import pytest
@@ -683,6 +684,110 @@ def test_denoise_step_ends_channels_and_widths(exp_d, adim, frame_dim):
         assert P.row_rel_err(f[i], xf) < P.TOL_BF16
         assert P.row_rel_err(a[i], xa) < P.TOL_BF16
     pol.close()
+
+
+def _fma32(a, b, c):
+    """fma of float32 arrays, rounded once: the product of two float32 is exact
+    in float64, the sum is rounded to odd there and then to nearest."""
+    p, c = a.astype(np.float64) * b.astype(np.float64), c.astype(np.float64)
+    p, c = np.broadcast_arrays(p, c)
+    s = p + c
+    t = s - p
+    err = (p - (s - t)) + (c - t)
+    bits = s.view(np.int64).copy()
+    odd = (err != 0) & (bits & 1 == 0)
+    bits[odd] += np.where((err > 0) == (s > 0), 1, -1)[odd]
+    return bits.view(np.float64).astype(np.float32)
+
+
+def _tree(x):
+    """Sum over the last axis (a power of two long): neighbours first."""
+    while x.shape[-1] > 1:
+        x = x[..., 0::2] + x[..., 1::2]
+    return x[..., 0]
+
+
+def _chains(a, b, cols):
+    """sum_k a[..., cols[k]] b[..., cols[k]]: an fma chain over k for each of the
+    64 columns of `cols`, then the tree."""
+    acc = np.zeros(np.broadcast_shapes(a.shape[:-1], b.shape[:-1]) + (64,), np.float32)
+    for c in cols:
+        acc = _fma32(a[..., c], b[..., c], acc)
+    return _tree(acc)
+
+
+@pytest.mark.parametrize("bf16,exp_d,adim,frame_dim", [(True, 256, 7, 32), (True, 1024, 18, 3), (True, 1536, 4, 16),
+                                                       (True, 192, 33, 20), (True, 1280, 5, 64), (False, 512, 7, 36)])
+def test_denoise_step_ends_keep_their_sum_order(bf16, exp_d, adim, frame_dim):
+    """Time MLP, input projection, output head and Euler update against the same
+    float32 sums in numpy, bit for bit, with the order that they are fixed to
+    (in the layers between, a changed rounding grows to 4e-4 of the actions).
+    O and down projections are zero, so that the layers pass the tokens on; the
+    time MLP's first weights are so large that SiLU is the identity or zero."""
+    rng = np.random.default_rng(exp_d + adim)
+    o = M.Config("ends", bf16=bf16, n_cams=0, img=0, patch=0, layers=1, d=64, q_heads=1, kv_heads=1, head_dim=64,
+                 mlp=64, vocab=64, n_lang=3, action_logits=False, exp_layers=1, exp_d=exp_d, exp_heads=1, exp_mlp=64,
+                 chunk=19, adim=adim, n_steps=2, frame_tokens=13, frame_dim=frame_dim)
+    f32, half, steps = np.float32, exp_d // 2, range(o.n_steps)
+
+    def weight(tid, rows, cols, std):
+        w = rng.normal(0, std, size=(rows, cols)).astype(f32)
+        if bf16:
+            w = (w.view(np.uint32) & np.uint32(0xFFFF0000)).view(f32)
+        pol.write_weight(tid, (w.view(np.uint32) >> 16).astype(np.uint16) if bf16 else w)
+        return w
+
+    ids = [0, 1]
+    pol = E.Policy(_ebrl_config(o, 2, 3), seed=0)
+    for slot, shape in ((3, (exp_d, 64)), (6, (exp_d, 64))):
+        weight(3000 + slot, *shape, 0.0)
+    t1, t2 = weight(8, exp_d, exp_d, 1e8), weight(9, exp_d, exp_d, 1e-9)
+    win = {"a": weight(7, exp_d, adim, 0.5), "f": weight(11, exp_d, frame_dim, 0.5)}
+    wout = {"a": weight(10, adim, exp_d, 0.02), "f": weight(12, frame_dim, exp_d, 0.02)}
+    x = {"a": rng.normal(size=(2, o.chunk, adim)).astype(f32),
+         "f": rng.normal(size=(2, o.frame_tokens, frame_dim)).astype(f32)}
+    pol.prefill(ids, lang_ids=_dev(synth_inputs.lang_ids(7, ids, 3, o.vocab)))
+    frames, actions = pol.wam_denoise(ids, _dev(x["f"]), _dev(x["a"]))
+    torch.cuda.synchronize()
+    frames, actions = frames.cpu().numpy(), actions.cpu().numpy()
+    v0 = np.stack([pol.read_state(E.STATE_FLOW_V0, e) for e in ids])
+    pol.close()
+
+    lane_strided = [np.arange(64) + 64 * i for i in range(exp_d // 64)]
+    fours = exp_d in (256, 512, 768, 1024, 1536, 2048)
+    head_cols = [256 * i + 4 * np.arange(64) + e for i in range(exp_d // 256) for e in range(4)] if fours else lane_strided
+
+    def ssq(h):
+        if fours:
+            return _chains(h, h, head_cols)
+        q = h.reshape(h.shape[:-1] + (exp_d // 4, 4))
+        q = _fma32(q[..., 3], q[..., 3], _fma32(q[..., 2], q[..., 2], _fma32(q[..., 0], q[..., 0], q[..., 1] * q[..., 1])))
+        q = np.concatenate([q, np.zeros(q.shape[:-1] + (-q.shape[-1] % 256,), f32)], -1)
+        per = np.zeros(q.shape[:-1] + (256,), f32)   # thread t takes quadruples t, t + 256, ..
+        for i in range(q.shape[-1] // 256):
+            per = per + q[..., 256 * i:256 * i + 256]
+        w = [_tree(per[..., 64 * i:64 * i + 64]) for i in range(4)]
+        return ((w[0] + w[1]) + w[2]) + w[3]
+
+    for k in steps:
+        a = [1000.0 * (1.0 - k / o.n_steps) * math.pow(10000.0, -j / half) for j in range(half)]
+        temb = np.array([math.sin(v) for v in a] + [math.cos(v) for v in a]).astype(f32)
+        mid = _chains(t1, temb[None], lane_strided)
+        assert np.abs(mid).min() > 120
+        tvec = _chains(t2, np.where(mid > 0, mid, f32(-0.0))[None], lane_strided)
+        for m in x:
+            h = np.zeros(x[m].shape[:2] + (exp_d,), f32)
+            for c in range(x[m].shape[2]):
+                h = _fma32(win[m][:, c], x[m][:, :, c, None], h)
+            h = h + tvec
+            rs = f32(1) / np.sqrt(ssq(h) / f32(exp_d) + f32(o.eps))
+            hn = h * rs[..., None]
+            vel = np.stack([_chains(hn, w, head_cols) for w in wout[m]], -1)
+            if m == "a" and k == 0:
+                assert np.array_equal(v0.reshape(vel.shape), vel)
+            x[m] = x[m] - vel / f32(o.n_steps)
+    assert np.array_equal(actions, x["a"])
+    assert np.array_equal(frames, x["f"])
 
 
 @pytest.mark.parametrize("model", ["flow", "wam"])
