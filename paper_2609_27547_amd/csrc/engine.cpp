@@ -1041,9 +1041,14 @@ int ebrl_policy_create(const ebrl_config* config, uint64_t seed, ebrl_policy** o
             (rc = dev_alloc_t(p, &p->flow_f, (size_t)c.max_envs * c.frame_tokens * c.frame_dim)))
             return bail(rc);
     }
-    // per-call metadata: generous bound on every call's int arrays
+    // per-call metadata: generous bound on the int arrays of a prefill (with the
+    // block table) or denoise call, and what a decode call takes: per row its
+    // env, per row and step a length and a row_dst entry
     p->meta_cap = 16 * (R + 64) + (size_t)c.max_envs * (32 + 2 * p->bt_stride) + p->bt_host.size() +
                   (size_t)c.max_envs * c.max_seq / 8 + 4096;
+    if (c.action_logits)
+        p->meta_cap = std::max(p->meta_cap, (size_t)std::min(p->dec_cap, DECODE_MAX_ROWS) *
+                                                    (1 + 3 * (size_t)std::max(c.n_action_tokens - 1, 1)) + 16);
     if ((rc = dev_alloc_t(p, &p->meta_dev, p->meta_cap))) return bail(rc);
     {
         void* hp = nullptr;

@@ -243,6 +243,29 @@ def test_action_head_wide_rows_and_partial_row_groups(bf16, n_bins, d, n):
     test_action_head_ragged_bins_rows_and_width(bf16, n_bins, d, n)
 
 
+@pytest.mark.parametrize("bf16,n,tokens", [(True, 64, 101), (False, 64, 101)])
+def test_decode_of_many_action_tokens_after_a_short_prefix(bf16, n, tokens):
+    """Far more action tokens than prefix: the call's per-step metadata, not the
+    prefix, sets its size.  All environments at once, a few of them against the
+    oracle, the last one alone with the same bits."""
+    cfg = M.Config("many", bf16=bf16, n_cams=0, img=1, patch=1, layers=1, d=64, q_heads=1, kv_heads=1, head_dim=64,
+                   mlp=64, vocab=64, n_lang=5, n_bins=32, n_action_tokens=tokens)
+    pol = E.Policy(_ebrl_config(cfg, n, 5), seed=3)
+    ids = list(range(n))
+    lang = synth_inputs.lang_ids(7, ids, 5, cfg.vocab)
+    pol.prefill(ids, lang_ids=_dev(lang))
+    tok, _, mar = pol.decode_actions(ids)
+    tok, mar = tok.cpu().numpy(), mar.cpu().numpy()
+    ref = M.Policy(cfg, seed=3)
+    for i in (0, n - 1):
+        r = ref.decode(ref.prefill(None, lang[i]), forced=tok[i, :-1])
+        P.check_tokens(tok[i], r, cfg.n_bins)
+        _check_margins(pol, ref, i, mar[i], r, P.TOL_BF16 if bf16 else P.TOL_FP32)
+    one, _, m1 = pol.decode_actions([ids[-1]])
+    assert np.array_equal(one.cpu().numpy()[0], tok[-1]) and np.array_equal(m1.cpu().numpy()[0], mar[-1])
+    pol.close()
+
+
 # ------------------------------------------------------- resident weights --
 
 @pytest.mark.parametrize("preset", [1, 2])
