@@ -25,6 +25,19 @@ extern "C" {
 int ebrl_op_gemm(int32_t dtype, const void* A, const void* B, float* C, int32_t M, int32_t N,
                  int32_t K, void* stream);
 
+/* The kernel that computes a product, for tests and timings that have to know
+ * which one they reach; host arithmetic, no GPU needed.  in_order 0: as
+ * ebrl_op_gemm; else as the prefill, ViT and expert projections, which sum K
+ * in order at any M.  cus: compute units of the stream (ebrl_op_gemm: 256).
+ * plan[0] 0: register-staged tiles (K not a multiple of 64), 1: 256 x 256
+ * tiles, 2: LDS ring, 3: decode, 4: fp32; [1], [2] tile rows and columns; [3]
+ * K splits; [4] workgroups; [5] K groups a decode wave keeps in LDS; [6], [7]
+ * kernel 1: tiles dealt evenly, and the parts each tile of the last round is
+ * cut into.  0 where it does not apply.  Returns EBRL_E_INVALID on bad
+ * arguments. */
+int ebrl_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t in_order, int32_t cus,
+                      int32_t plan[8]);
+
 /* For callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  The same
  * product as ebrl_op_gemm, bit for bit (same kernels and the same tile and

@@ -1554,6 +1554,13 @@ int ebrl_op_gemm(int32_t dtype, const void* A, const void* B, float* C, int32_t 
     return hipGetLastError() == hipSuccess ? EBRL_OK : EBRL_E_HIP;
 }
 
+int ebrl_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t in_order, int32_t cus, int32_t* plan) {
+    if (!plan || M < 1 || N < 1 || K < 8 || K % 8 || N % 4 || cus < 1) return EBRL_E_INVALID;
+    if (dtype != EBRL_DTYPE_BF16 && dtype != EBRL_DTYPE_FP32) return EBRL_E_INVALID;
+    ebrl::gemm_plan_info(dtype == EBRL_DTYPE_BF16, M, N, K, OP_WS_FLOATS, !in_order && M < 256, std::min(cus, 256), plan);
+    return EBRL_OK;
+}
+
 // ebrl_op_gemm_noalloc: the same product with its split-K partials and tile
 // counters in `scratch`, a fixed device array each GPU holds for the whole
 // process, instead of memory the library allocates.  The array's name in

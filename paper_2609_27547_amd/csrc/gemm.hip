@@ -817,7 +817,16 @@ EBRL_DEV bf16x8 dec_frag(const bf16_t* lds, int row, int c) {
     return *reinterpret_cast<const bf16x8*>(lds + (row >> 3) * 512 + ((row & 7) * 8 + (c ^ (row & 7))) * 8);
 }
 
-template <int TM, int BN, bool NTW, bool NORM, bool PAIRED, class Epi>
+// K groups per wave in LDS, all but the one being multiplied in flight: three
+// for 64-column slices where they fit (measured 1-13 % more bandwidth than two
+// on the 7B-class decode shapes at 1-32 rows), two for 96-column slices (all of
+// the LDS at 64 rows) and for 32-column ones, or four there where one workgroup
+// has a CU to itself (plan_gemm).
+constexpr int dec_stages(int tm, int bn, bool deep) {
+    return bn == 96 ? 2 : bn == 32 ? (deep ? 4 : 2) : (3 * 4 * (bn + 16 * tm) * 128 <= 150 * 1024 ? 3 : 2);
+}
+
+template <int TM, int BN, bool NTW, bool DEEP, bool NORM, bool PAIRED, class Epi>
 __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int ldw, int M, int N,
     int K, int groups_per_split, int splits, int m_tiles, float* __restrict__ ws,
@@ -829,15 +838,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
     constexpr int WE = BN * 64;            // bf16 per wave per buffer: weights
     constexpr int XE = TM * 16 * 64;       //                             activations
     constexpr int NDMA = (BN + TM * 16) / 8;       // DMA instructions per K group
-    // K groups per wave in LDS, all but the one being multiplied in flight:
-    // three for 64-column slices where they fit (measured 1-13 % more
-    // bandwidth than two on the 7B-class decode shapes at 1-32 rows), two for
-    // 96-column slices (all of the LDS at 64 rows).  32-column slices of up to
-    // 32 rows run one workgroup per CU and are held by latency, not bytes: four
-    // (one row, K 1024 to 4096: 6.2 -> 5.6 us and 7.2 -> 6.4 us against two); at 64
-    // rows three are slower than two (7.5 -> 8.1 us).
     constexpr int STAGE = (WE + XE) * 2;   // bytes per wave and group
-    constexpr int STAGES = BN == 96 ? 2 : BN == 32 ? (TM <= 2 ? 4 : 2) : (3 * 4 * STAGE <= 150 * 1024 ? 3 : 2);
+    constexpr int STAGES = dec_stages(TM, BN, DEEP);
     __shared__ __attribute__((aligned(1024))) char smem[4 * STAGES * STAGE];
     // After the main loop (every DMA landed, a barrier passed) it holds the
     // waves' tiles for the reduction, the per-row sums of squares and the
@@ -874,11 +876,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
     const int w_begin = min(s_end, s_begin + wave * gpw);
     const int w_end = min(s_end, w_begin + gpw);
 
-    // buffer b of this wave: BN weight rows, then 16 TM activation rows
+    // this wave's buffers: BN weight rows, then 16 TM activation rows each
     auto buf = [&](int b) { return reinterpret_cast<bf16_t*>(smem + (wave * STAGES + b) * STAGE); };
-    auto dma = [&](int grp, int b) {
-        dec_dma<BN, NTW>(W, ldw, n0, N, grp * 64, buf(b), lane);
-        dec_dma<TM * 16>(A, lda, m0, M, grp * 64, buf(b) + WE, lane);
+    auto dma = [&](int grp, bf16_t* to) {
+        dec_dma<BN, NTW>(W, ldw, n0, N, grp * 64, to, lane);
+        dec_dma<TM * 16>(A, lda, m0, M, grp * 64, to + WE, lane);
     };
 
     // Output units: one fragment lane (or a gate/up fragment pair) each.
@@ -908,7 +910,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
 #pragma unroll
     for (int i = 0; i < TM; ++i) ssq[i] = 0.f;
     // both 32-wide steps of a K group: fragment reads first, then the MFMAs
-    auto compute = [&](const bf16_t* wl, const bf16_t* xl) {
+    auto compute = [&](const bf16_t* wl) {
+        const bf16_t* const xl = wl + WE;
         bf16x8 wa[2][TN], xb[2][TM];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -941,20 +944,68 @@ __global__ __launch_bounds__(256) void gemm_bf16_decode_kernel(
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u][j], xb[u][i], acc[i][j], 0, 0, 0);
     };
 
-    // group w_begin + i sits in buffer i % STAGES; multiplying it first puts
+    // Group w_begin + i sits in buffer i % STAGES; multiplying it first puts
     // the group STAGES - 1 further on in flight, into the buffer that the
-    // group before it has left
+    // group before it has left (wait_lds: that one has been read).  Two and three
+    // buffers as plain code: one loop over all depths costs the launches of
+    // several row tiles 1-3 % (80 x 8192 x 1024: 9.14 -> 9.36 us).
+    if constexpr (STAGES == 2) {
+        bf16_t* const b0 = buf(0);
+        bf16_t* const b1 = buf(1);
+        auto step = [&](int gi, bf16_t* cur, bf16_t* nxt) {
+            wait_lds();
+            if (gi + 1 < w_end) {
+                dma(gi + 1, nxt);
+                wait_vmcnt<NDMA>();
+            } else {
+                wait_vmcnt<0>();
+            }
+            compute(cur);
+        };
+        if (w_begin < w_end) dma(w_begin, b0);
+        for (int gi = w_begin; gi < w_end; gi += 2) {
+            step(gi, b0, b1);
+            if (gi + 1 >= w_end) break;
+            step(gi + 1, b1, b0);
+        }
+    } else if constexpr (STAGES == 3) {
+        bf16_t* const b0 = buf(0);
+        bf16_t* const b1 = buf(1);
+        bf16_t* const b2 = buf(2);
+        auto step = [&](int gi, bf16_t* cur, bf16_t* nxt) {
+            wait_lds();
+            if (gi + 2 < w_end) {
+                dma(gi + 2, nxt);
+                wait_vmcnt<2 * NDMA>();
+            } else if (gi + 1 < w_end) {
+                wait_vmcnt<NDMA>();
+            } else {
+                wait_vmcnt<0>();
+            }
+            compute(cur);
+        };
+        if (w_begin < w_end) dma(w_begin, b0);
+        if (w_begin + 1 < w_end) dma(w_begin + 1, b1);
+        for (int gi = w_begin; gi < w_end; gi += 3) {
+            step(gi, b0, b2);
+            if (gi + 1 >= w_end) break;
+            step(gi + 1, b1, b0);
+            if (gi + 2 >= w_end) break;
+            step(gi + 2, b2, b1);
+        }
+    } else {
 #pragma unroll
-    for (int i = 0; i < STAGES - 1; ++i)
-        if (w_begin + i < w_end) dma(w_begin + i, i);
-    for (int gi = w_begin; gi < w_end; gi += STAGES) {
+        for (int i = 0; i < STAGES - 1; ++i)
+            if (w_begin + i < w_end) dma(w_begin + i, buf(i));
+        for (int gi = w_begin; gi < w_end; gi += STAGES) {
 #pragma unroll
-        for (int i = 0; i < STAGES; ++i) {
-            if (gi + i >= w_end) break;
-            wait_lds();   // the buffer refilled next has been read
-            if (gi + i + STAGES - 1 < w_end) dma(gi + i + STAGES - 1, (i + STAGES - 1) % STAGES);
-            wait_tiles<STAGES - 1, NDMA>(w_end - 1 - gi - i);
-            compute(buf(i), buf(i) + WE);
+            for (int i = 0; i < STAGES; ++i) {
+                if (gi + i >= w_end) break;
+                wait_lds();
+                if (gi + i + STAGES - 1 < w_end) dma(gi + i + STAGES - 1, buf((i + STAGES - 1) % STAGES));
+                wait_tiles<STAGES - 1, NDMA>(w_end - 1 - gi - i);
+                compute(buf(i));
+            }
         }
     }
 
@@ -1233,7 +1284,7 @@ struct GemmPlan {
     int bm; int splits; int k_per_split;
     bool seq;      // K in order: the large-M kernel (bm 256) or the ring kernel (bm x bn)
     int bn; int grid, full, split;   // large-M kernel: workgroups, evenly dealt tiles, cut of the last round's tiles
-    bool dec; int steps_per_split; int tm; int m_tiles; int dbn;   // decode kernel (steps: 64-wide K groups)
+    bool dec; int steps_per_split; int tm; int m_tiles; int dbn; bool deep;   // decode kernel (steps: 64-wide K groups)
 };
 
 // Kernel and split choice.  The tile variant never changes an element's
@@ -1330,6 +1381,17 @@ static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool
             };
             if (cost(96) < cost(64)) p.dbn = 96;
         }
+        // 32-column slices of up to 32 rows keep four K groups in LDS where
+        // every workgroup has a CU to itself: those launches are held by
+        // latency (one row, weights from HBM as in a policy: 4096 x 4096 11.8 ->
+        // 9.9 us, 3072 x 1024 4.40 -> 4.17; 17 rows of 4096 x 4096 11.8 -> 10.1;
+        // weights left in L2 by the last call: 7.3 -> 6.9, 2.93 -> 3.11 and 7.5 ->
+        // 8.4).  With more workgroups than CUs the 96 or 128 KB would leave one on a CU and the rest to a
+        // second round, where two groups let two or three share it (3072
+        // outputs, K 1024, 288 workgroups: 5.1 us with four, 3.8 with two at 40
+        // rows, 6.3 and 4.7 at 80); 64 rows are slower with more than two as
+        // well (7.5 -> 8.1 us).
+        p.deep = p.dbn == 32 && p.tm <= 2 && (long)((N + 31) / 32) * p.splits * p.m_tiles <= cus;
         return p;
     }
     if (bf16 && !split_ok && K % 64 == 0) {
@@ -1389,22 +1451,24 @@ static void launch_bf16(const GemmArgs& a, const GemmPlan& p, Epi epi, hipStream
         auto pick = [&](auto NORM) {
             constexpr bool NM = decltype(NORM)::value;
             if (p.dbn == 96) {   // row tiles of 16 or 32 rows: one tile (plan_gemm)
-                if (p.tm == 1) godec(gemm_bf16_decode_kernel<1, 96, true, NM, PAIRED, Epi>, 96);
-                else if (p.tm == 2) godec(gemm_bf16_decode_kernel<2, 96, true, NM, PAIRED, Epi>, 96);
-                else if (p.m_tiles == 1) godec(gemm_bf16_decode_kernel<4, 96, true, NM, PAIRED, Epi>, 96);
-                else godec(gemm_bf16_decode_kernel<4, 96, false, NM, PAIRED, Epi>, 96);
+                if (p.tm == 1) godec(gemm_bf16_decode_kernel<1, 96, true, false, NM, PAIRED, Epi>, 96);
+                else if (p.tm == 2) godec(gemm_bf16_decode_kernel<2, 96, true, false, NM, PAIRED, Epi>, 96);
+                else if (p.m_tiles == 1) godec(gemm_bf16_decode_kernel<4, 96, true, false, NM, PAIRED, Epi>, 96);
+                else godec(gemm_bf16_decode_kernel<4, 96, false, false, NM, PAIRED, Epi>, 96);
             } else if (p.dbn == 32) {
-                if (p.tm == 1) godec(gemm_bf16_decode_kernel<1, 32, false, NM, PAIRED, Epi>, 32);
-                else if (p.tm == 2) godec(gemm_bf16_decode_kernel<2, 32, false, NM, PAIRED, Epi>, 32);
-                else godec(gemm_bf16_decode_kernel<4, 32, false, NM, PAIRED, Epi>, 32);
+                if (p.tm == 4) godec(gemm_bf16_decode_kernel<4, 32, false, false, NM, PAIRED, Epi>, 32);
+                else if (p.tm == 2 && p.deep) godec(gemm_bf16_decode_kernel<2, 32, false, true, NM, PAIRED, Epi>, 32);
+                else if (p.tm == 2) godec(gemm_bf16_decode_kernel<2, 32, false, false, NM, PAIRED, Epi>, 32);
+                else if (p.deep) godec(gemm_bf16_decode_kernel<1, 32, false, true, NM, PAIRED, Epi>, 32);
+                else godec(gemm_bf16_decode_kernel<1, 32, false, false, NM, PAIRED, Epi>, 32);
             } else if (p.m_tiles == 1) {
-                if (p.tm == 1) godec(gemm_bf16_decode_kernel<1, 64, true, NM, PAIRED, Epi>, 64);
-                else if (p.tm == 2) godec(gemm_bf16_decode_kernel<2, 64, true, NM, PAIRED, Epi>, 64);
-                else godec(gemm_bf16_decode_kernel<4, 64, true, NM, PAIRED, Epi>, 64);
+                if (p.tm == 1) godec(gemm_bf16_decode_kernel<1, 64, true, false, NM, PAIRED, Epi>, 64);
+                else if (p.tm == 2) godec(gemm_bf16_decode_kernel<2, 64, true, false, NM, PAIRED, Epi>, 64);
+                else godec(gemm_bf16_decode_kernel<4, 64, true, false, NM, PAIRED, Epi>, 64);
             } else {
-                if (p.tm == 1) godec(gemm_bf16_decode_kernel<1, 64, false, NM, PAIRED, Epi>, 64);
-                else if (p.tm == 2) godec(gemm_bf16_decode_kernel<2, 64, false, NM, PAIRED, Epi>, 64);
-                else godec(gemm_bf16_decode_kernel<4, 64, false, NM, PAIRED, Epi>, 64);
+                if (p.tm == 1) godec(gemm_bf16_decode_kernel<1, 64, false, false, NM, PAIRED, Epi>, 64);
+                else if (p.tm == 2) godec(gemm_bf16_decode_kernel<2, 64, false, false, NM, PAIRED, Epi>, 64);
+                else godec(gemm_bf16_decode_kernel<4, 64, false, false, NM, PAIRED, Epi>, 64);
             }
         };
         // the folded RMSNorm exists for the projections that follow a norm
@@ -1509,6 +1573,29 @@ int gemm(const GemmArgs& a, hipStream_t s) {
         return dispatch<true>(a, make_epi_qkv<float>(*a.rope), s);
     }
     return 0;
+}
+
+void gemm_plan_info(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok, int cus, int32_t* out) {
+    std::fill(out, out + 8, 0);
+    out[3] = 1;
+    if (!bf16) { out[0] = GEMM_K_FP32; return; }
+    const GemmPlan p = plan_gemm(true, M, N, K, ws_floats, split_ok && M <= SPLIT_MAX_M, cus);
+    out[3] = p.splits;
+    if (p.dec) {
+        out[0] = GEMM_K_DECODE;
+        out[1] = 16 * p.tm;
+        out[2] = p.dbn;
+        out[4] = ((N + p.dbn - 1) / p.dbn) * p.splits * p.m_tiles;
+        out[5] = dec_stages(p.tm, p.dbn, p.deep);
+    } else if (p.seq) {
+        out[0] = p.bm == 256 ? GEMM_K_LARGE : GEMM_K_RING;
+        out[1] = p.bm;
+        out[2] = p.bn;
+        out[4] = p.bm == 256 ? p.grid : ((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn);
+        if (p.bm == 256) { out[6] = p.full; out[7] = p.split; }
+    } else {
+        out[0] = GEMM_K_TILES;
+    }
 }
 
 int gemm_splits(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok) {

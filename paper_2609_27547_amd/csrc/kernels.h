@@ -60,6 +60,12 @@ constexpr int DECODE_MAX_ROWS = 256;
 // Returns the number of K splits used (1 = single pass).
 int gemm(const GemmArgs& a, hipStream_t s);
 int gemm_splits(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok);
+// What gemm() launches for a product: {kernel, tile rows, tile columns, K splits,
+// workgroups, LDS stages of the decode kernel, tiles that the large-M kernel
+// deals evenly, parts that it cuts each other tile into}; what a kernel has not
+// is 0.
+enum { GEMM_K_TILES = 0, GEMM_K_LARGE, GEMM_K_RING, GEMM_K_DECODE, GEMM_K_FP32 };
+void gemm_plan_info(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok, int cus, int32_t* out);
 bool gemm_row_norm_ok(bool bf16, int M, int N, int K, size_t ws_floats);
 size_t gemm_counter_words();
 // Workspace floats the plan for (M, N, K) writes (0 without a K split).

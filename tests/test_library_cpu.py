@@ -64,3 +64,24 @@ def test_host_weight_generator_bitwise_equals_oracle(bf16):
     a = E.generate_weight_host(123456789012345, 2, 5000, 0.02, bf16)
     b = M.gen_tensor(123456789012345, 2, (5000,), 0.02, bf16)
     assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
+
+
+@pytest.mark.parametrize("cus", [256, 192, 100, 32])
+def test_decode_gemm_keeps_four_groups_only_where_a_workgroup_has_a_cu(cus):
+    """Four K groups a wave leave room for one workgroup on a CU: more
+    workgroups than CUs would run in a second round, so those plans keep two."""
+    deep = 0
+    for n in range(64, 8193, 64):
+        for k in (256, 1024, 4096, 11008):
+            for m in (1, 16, 17, 33, 40, 64, 65, 80, 96, 128):
+                p = E.op_gemm_plan(m, n, k, cus=cus)
+                assert p["kernel"] == "decode"
+                if p["stages"] == 4:
+                    deep += 1
+                    assert p["cols"] == 32 and p["workgroups"] <= cus, (m, n, k, p)
+    assert deep
+    if cus == 256:
+        assert E.op_gemm_plan(1, 4096, 4096)["stages"] == 4
+        for m in (33, 48, 65, 96):   # the small policy's QKV: 288 workgroups
+            p = E.op_gemm_plan(m, 3072, 1024)
+            assert p["workgroups"] == 288 and p["stages"] == 2
