@@ -28,7 +28,7 @@ int ebrl_op_gemm(int32_t dtype, const void* A, const void* B, float* C, int32_t 
 /* The kernel that computes a product, for tests and timings that have to know
  * which one they reach; host arithmetic, no GPU needed.  in_order 0: as
  * ebrl_op_gemm; else as the prefill, ViT and expert projections, which sum K
- * in order at any M.  cus: compute units of the stream (ebrl_op_gemm: 256).
+ * in order at any M (with ebrl_op_gemm's output).  cus: compute units of the stream (ebrl_op_gemm: 256).
  * plan[0] 0: register-staged tiles (K not a multiple of 64), 1: 256 x 256
  * tiles, 2: LDS ring, 3: decode, 4: fp32; [1], [2] tile rows and columns; [3]
  * K splits; [4] workgroups; [5] K groups a decode wave keeps in LDS; [6], [7]

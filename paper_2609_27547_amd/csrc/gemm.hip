@@ -1292,27 +1292,57 @@ struct GemmPlan {
 constexpr int SPLIT_MAX_M = DECODE_MAX_ROWS;
 
 // Projections that sum K in order (prefill, ViT, experts): the kernel whose
-// modelled time is least.  Both are bound by what a CU streams, so a tile's
-// time per 64-wide K tile is a constant of its shape (us, measured on one
-// MI355X with every CU busy): 1.2 for 256 x 256, and for the last round's cut
-// tiles 0.70 (128 x 256) and 0.45 (128 x 128); ring tiles at least 0.37 (64 x
-// 128), 0.24 (64 x 64), 0.19 (32 x 64), and BM + BN rows of 128 bytes at 70
-// GB/s per CU where several tiles share it.  The constants 3.5 and 2.4 us are
-// launch, first loads and epilogue.  No choice changes a sum's order.
-static void plan_in_order(GemmPlan& p, int M, int N, int K, int cus) {
+// modelled time (us) is least.  The constants are a fit to all six variants on
+// 184 products (fp32 output, M 257 to 8192, N 1024 to 22016, K 1024 to 11008, 256
+// CUs; modelled times scatter by 5 %), and to the projections of 33 policy calls,
+// each run with all six.  The variant it picks is on average 0.3 % (at worst 8 %)
+// slower than the best one on the products, and costs the calls 0.1 % a projection;
+// one constant per variant and no rounds cost 1.4 % and 0.3 % (640 x 4096 x 11008 104
+// us instead of 79, 300 x 12288 x 4096 52 instead of 45).  No choice changes a sum's
+// order.
+// `extra`: how much longer a tile's epilogue takes the large kernel than the
+// ring, whose other workgroup on the CU multiplies meanwhile (0 for plain stores
+// and SwiGLU).
+static void plan_in_order(GemmPlan& p, int M, int N, int K, int cus, double extra) {
     const double nk = K / 64;
-    const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
-    const long full = tiles / cus * cus, rest = tiles - full;
+    auto up = [](long a, long b) { return (a + b - 1) / b; };
+    const long tiles = up(M, 256) * up(N, 256);
+    const long rounds = tiles / cus, full = rounds * cus, rest = tiles - full;
     p.seq = true;
     p.bm = p.bn = 256;
-    p.split = rest * 4 <= cus ? 4 : rest * 2 <= cus ? 2 : 1;
     p.full = (int)full;
+    double best = 0;
+    // 256 x 256 tiles: whole rounds, then the remaining tiles whole or cut in
+    // two or four where the pieces fit one round.  A K tile of a piece takes
+    // `alone` with the chip nearly empty and `busy` with a piece on every CU.
+    struct Cut { int split; double c, alone, busy; } cuts[] = {{1, 8.0, 0.75, 1.24}, {2, 5.6, 0.50, 0.78}, {4, 4.0, 0.38, 0.55}};
+    for (const Cut& v : cuts) {
+        if (v.split > 1 && (!rest || rest * v.split > cus)) continue;
+        // (pieces past the last row or column have nothing to do)
+        const long pieces = full || v.split == 1 ? rest * v.split : up(M, 128) * up(N, v.split == 2 ? 256 : 128);
+        double t = v.c + extra + rounds * (8.7 + 1.39 * nk);
+        if (rest) t += nk * (v.alone + (v.busy - v.alone) * pieces / cus);
+        if (v.split == 1 || t < best) {
+            best = t;
+            p.split = v.split;
+        }
+    }
     p.grid = (int)(full ? cus : rest * p.split);
-    double best = 3.5 + nk * (1.2 * (tiles / cus) + (!rest ? 0 : p.split == 4 ? 0.45 : p.split == 2 ? 0.70 : 1.1));
-    struct V { int bm, bn; double least; } vs[] = {{64, 128, 0.37}, {64, 64, 0.24}, {32, 64, 0.19}};
-    for (const V& v : vs) {
-        const double per_cu = (double)((M + v.bm - 1) / v.bm) * ((N + v.bn - 1) / v.bn) / cus;
-        const double t = 2.4 + nk * std::max(v.least, per_cu * (v.bm + v.bn) * 128 / 70e3);
+    // Ring tiles: two workgroups share a CU, so they take rounds of one (`one`
+    // us a K tile) or two (`two`) a CU.  Each group of four row tiles streams the
+    // weights once: the first at 5.5 TB/s, the others, on other XCDs, at 3.6; of
+    // that and the K loop the shorter one shows by a tenth.
+    struct Ring { int bm, bn; double c, epi, one, two; } rings[] = {{64, 128, 2.4, 1.7, 0.353, 0.610},
+                                                                    {64, 64, 2.3, 1.0, 0.225, 0.355},
+                                                                    {32, 64, 2.4, 0.7, 0.175, 0.262}};
+    for (const Ring& v : rings) {
+        const long wgs = up(M, v.bm) * up(N, v.bn), pairs = wgs / (2 * cus);
+        const double left = (double)(wgs - pairs * 2 * cus) / cus;   // workgroups a CU in the last round
+        double t = v.c + pairs * (v.epi + nk * v.two);
+        if (left > 1) t += v.epi + nk * (v.one + (v.two - v.one) * (0.6 + 0.4 * (left - 1)));
+        else if (left > 0) t += v.epi / 2 + nk * v.one;
+        const double w = (double)N * K * 2e-6 * (1 / 5.5 + (up(up(M, v.bm), 4) - 1) / 3.6);
+        t = std::max(t, w) + 0.1 * std::min(t, w);
         if (t < best) {
             best = t;
             p.bm = v.bm;
@@ -1321,7 +1351,8 @@ static void plan_in_order(GemmPlan& p, int M, int N, int K, int cus) {
     }
 }
 
-static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok, int cus = 256) {
+static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok, int cus = 256,
+                          double extra = 0) {
     GemmPlan p;
     p.seq = false;
     p.dec = false;
@@ -1395,7 +1426,7 @@ static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool
         return p;
     }
     if (bf16 && !split_ok && K % 64 == 0) {
-        plan_in_order(p, M, N, K, cus);
+        plan_in_order(p, M, N, K, cus, extra);
         return p;
     }
     if (M <= 16) p.bm = 16;
@@ -1543,7 +1574,8 @@ template <bool PAIRED, class Epi>
 static int dispatch(const GemmArgs& a, Epi epi, hipStream_t s) {
     const GemmPlan p = plan_gemm(a.bf16, a.M, a.N, a.K, a.ws_floats,
                                  a.split_ok && a.M <= SPLIT_MAX_M && (!a.bf16 || a.counters),
-                                 std::max(1, std::min(a.cus, 256)));
+                                 std::max(1, std::min(a.cus, 256)),
+                                 a.epi == EPI_QKV ? 6.0 : a.epi == EPI_RESID ? 1.5 : 0.0);
     if (a.bf16) launch_bf16<PAIRED>(a, p, epi, s);
     else launch_f32<PAIRED>(a, epi, s);
     return p.splits;

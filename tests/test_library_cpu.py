@@ -85,3 +85,17 @@ def test_decode_gemm_keeps_four_groups_only_where_a_workgroup_has_a_cu(cus):
         for m in (33, 48, 65, 96):   # the small policy's QKV: 288 workgroups
             p = E.op_gemm_plan(m, 3072, 1024)
             assert p["workgroups"] == 288 and p["stages"] == 2
+
+
+@pytest.mark.parametrize("m,n,k,kernel,cols,cut", [
+    # shapes at which the best kernel is 4 % or more ahead of the others
+    (257, 12288, 4096, "large", 256, 2), (300, 12288, 4096, "large", 256, 2), (300, 8192, 1024, "large", 256, 4),
+    (640, 4096, 11008, "large", 256, 4), (1100, 2048, 8192, "large", 256, 4), (2304, 1024, 4096, "large", 256, 4),
+    (3200, 1024, 4096, "large", 256, 4), (3200, 8192, 1024, "large", 256, 1), (8192, 22016, 4096, "large", 256, 0),
+    (257, 2048, 8192, "ring", 64, 0), (424, 4096, 4096, "ring", 64, 0), (640, 2048, 8192, "ring", 64, 0),
+    (800, 1024, 4096, "ring", 64, 0), (424, 1024, 4096, "ring", 64, 0)])
+def test_in_order_gemm_plan_is_the_measured_best(m, n, k, kernel, cols, cut):
+    p = E.op_gemm_plan(m, n, k, in_order=True)
+    assert (p["kernel"], p["cols"]) == (kernel, cols), p
+    if cut:
+        assert p["cut"] == cut, p
