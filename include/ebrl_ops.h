@@ -18,7 +18,7 @@ extern "C" {
  * path, fp32 accumulate); EBRL_DTYPE_FP32: float32.  C is float32 row-major
  * with leading dimension N.  Requires M, N >= 1, K >= 8 and K % 8 == 0;
  * the kernel choice (tile, split over K) depends only on (M, N, K).
- * stream: hipStream_t or NULL.  K splits (M < 256) write their partial sums
+ * stream: hipStream_t or NULL.  K splits (bf16, M < 256) write their partial sums
  * to a workspace the library allocates on the first call per (device,
  * stream) and keeps until the process ends, so calls on different streams
  * may overlap.  Returns EBRL_E_OOM if that allocation fails. */
@@ -46,7 +46,7 @@ int ebrl_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t in
  * each GPU the library runs on holds until the process ends; the call
  * allocates nothing and issues no memset.  Shapes whose split would write
  * more partial sums than the array holds return EBRL_E_INVALID (without a
- * split, e.g. M >= 256, any shape is accepted).  Every call on one GPU shares
+ * split, i.e. M >= 256 or fp32, any shape is accepted).  Every call on one GPU shares
  * that GPU's array: calls that overlap in time on one GPU (on different
  * streams or from different host threads) race and give wrong results;
  * calls ordered on one stream do not.  Same arguments and errors as

@@ -1351,14 +1351,14 @@ static void plan_in_order(GemmPlan& p, int M, int N, int K, int cus, double extr
     }
 }
 
-static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok, int cus = 256,
-                          double extra = 0) {
+// bf16 products
+static GemmPlan plan_gemm(int M, int N, int K, size_t ws_floats, bool split_ok, int cus = 256, double extra = 0) {
     GemmPlan p;
     p.seq = false;
     p.dec = false;
     p.splits = 1;
     p.k_per_split = K;
-    if (bf16 && split_ok && K % 64 == 0) {
+    if (split_ok && K % 64 == 0) {
         // K splits: about 64 (column slice, split) pairs, each split at least
         // 16 K groups (1024 wide) -- the cross-workgroup hand-off costs about
         // as much as streaming that much more.  Narrow outputs with a long K
@@ -1425,7 +1425,7 @@ static GemmPlan plan_gemm(bool bf16, int M, int N, int K, size_t ws_floats, bool
         p.deep = p.dbn == 32 && p.tm <= 2 && (long)((N + 31) / 32) * p.splits * p.m_tiles <= cus;
         return p;
     }
-    if (bf16 && !split_ok && K % 64 == 0) {
+    if (K % 64 == 0) {
         plan_in_order(p, M, N, K, cus, extra);
         return p;
     }
@@ -1572,12 +1572,14 @@ static void launch_f32(const GemmArgs& a, Epi epi, hipStream_t s) {
 
 template <bool PAIRED, class Epi>
 static int dispatch(const GemmArgs& a, Epi epi, hipStream_t s) {
-    const GemmPlan p = plan_gemm(a.bf16, a.M, a.N, a.K, a.ws_floats,
-                                 a.split_ok && a.M <= SPLIT_MAX_M && (!a.bf16 || a.counters),
+    if (!a.bf16) {   // one launch, K split inside the workgroup
+        launch_f32<PAIRED>(a, epi, s);
+        return 1;
+    }
+    const GemmPlan p = plan_gemm(a.M, a.N, a.K, a.ws_floats, a.split_ok && a.M <= SPLIT_MAX_M && a.counters,
                                  std::max(1, std::min(a.cus, 256)),
                                  a.epi == EPI_QKV ? 6.0 : a.epi == EPI_RESID ? 1.5 : 0.0);
-    if (a.bf16) launch_bf16<PAIRED>(a, p, epi, s);
-    else launch_f32<PAIRED>(a, epi, s);
+    launch_bf16<PAIRED>(a, p, epi, s);
     return p.splits;
 }
 
@@ -1611,7 +1613,7 @@ void gemm_plan_info(bool bf16, int M, int N, int K, size_t ws_floats, bool split
     std::fill(out, out + 8, 0);
     out[3] = 1;
     if (!bf16) { out[0] = GEMM_K_FP32; return; }
-    const GemmPlan p = plan_gemm(true, M, N, K, ws_floats, split_ok && M <= SPLIT_MAX_M, cus);
+    const GemmPlan p = plan_gemm(M, N, K, ws_floats, split_ok && M <= SPLIT_MAX_M, cus);
     out[3] = p.splits;
     if (p.dec) {
         out[0] = GEMM_K_DECODE;
@@ -1630,14 +1632,10 @@ void gemm_plan_info(bool bf16, int M, int N, int K, size_t ws_floats, bool split
     }
 }
 
-int gemm_splits(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok) {
-    return plan_gemm(bf16, M, N, K, ws_floats, split_ok && M <= SPLIT_MAX_M).splits;
-}
-
 bool gemm_row_norm_ok(bool bf16, int M, int N, int K, size_t ws_floats) {
     if (!bf16) return true;   // one workgroup always sees the whole K
     if (M > SPLIT_MAX_M || K % 64) return false;
-    const GemmPlan p = plan_gemm(true, M, N, K, ws_floats, true);
+    const GemmPlan p = plan_gemm(M, N, K, ws_floats, true);
     return p.dec && p.splits == 1;
 }
 
@@ -1645,11 +1643,9 @@ size_t gemm_counter_words() {
     return DEC_MAX_COUNTERS;
 }
 
-// fp32 products write no partial sums; the count of the plan that once split
-// them is kept as what ebrl_op_gemm_noalloc accepts, so that no shape changes
-// sides.
 size_t gemm_ws_floats_used(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok) {
-    const GemmPlan p = plan_gemm(bf16, M, N, K, ws_floats, split_ok && M <= SPLIT_MAX_M);
+    if (!bf16) return 0;
+    const GemmPlan p = plan_gemm(M, N, K, ws_floats, split_ok && M <= SPLIT_MAX_M);
     if (p.splits <= 1) return 0;
     if (p.dec) return (size_t)((N + p.dbn - 1) / p.dbn) * p.m_tiles * p.splits * DEC_TILE_FLOATS;
     return (size_t)p.splits * M * N;

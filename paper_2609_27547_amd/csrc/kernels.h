@@ -59,7 +59,6 @@ struct GemmArgs {
 constexpr int DECODE_MAX_ROWS = 256;
 // Returns the number of K splits used (1 = single pass).
 int gemm(const GemmArgs& a, hipStream_t s);
-int gemm_splits(bool bf16, int M, int N, int K, size_t ws_floats, bool split_ok);
 // What gemm() launches for a product: {kernel, tile rows, tile columns, K splits,
 // workgroups, LDS stages of the decode kernel, tiles that the large-M kernel
 // deals evenly, parts that it cuts each other tile into}; what a kernel has not

@@ -53,6 +53,12 @@ def test_noalloc_gemm_equals_allocating_entry_point(m, n, k, dtype):
     assert P.row_rel_err(got.cpu().numpy(), M.linear(a64, b64)) < 2e-6
 
 
+def test_noalloc_fp32_gemm_has_no_split_to_refuse():
+    """fp32 products split K inside a workgroup: a shape whose bf16 product is
+    refused below writes no partial sums and is computed."""
+    test_noalloc_gemm_equals_allocating_entry_point(200, 4096, 4104, "fp32")
+
+
 def test_noalloc_gemm_refuses_a_split_larger_than_its_scratch():
     # 200 x 4096 x 4104 splits K 13 ways over 200 x 4096 partial sums each
     # (10.6 M floats), more than the 16 MB array holds
