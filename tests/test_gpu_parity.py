@@ -134,16 +134,19 @@ def test_op_gemm_concurrent_streams_keep_their_own_split_workspace():
 def test_large_gemm_tile_variants_agree_bitwise():
     """The tiles of a prefill-sized product follow the shape: with 4092 columns
     (ragged against both 256 and 128), 9200 rows take two rounds of 256 x 256
-    tiles and a third of cut ones (the last row tile ragged), 4096 rows one
-    round, 2048 and 1000 rows cut tiles only.  The rows the calls share are
-    bitwise equal (every variant runs the same K order), and the full product
-    matches the definition."""
+    tiles and a third of cut ones (the last row tile ragged), 4096 rows ring
+    tiles, 2048 and 1000 rows halves and quarters of tiles only.  The rows the
+    calls share are bitwise equal (every variant runs the same K order), and
+    the full product matches the definition."""
     rng = np.random.default_rng(9200)
     K = 192
     a = rng.normal(size=(9200, K)).astype(np.float32)
     b = rng.normal(size=(4092, K)).astype(np.float32)
     A = torch.from_numpy(a).to(torch.bfloat16).cuda()
     B = torch.from_numpy(b).to(torch.bfloat16).cuda()
+    plans = {m: E.op_gemm_plan(m, 4092, K) for m in (9200, 4096, 2048, 1000)}
+    assert [(p["kernel"], p["even"], p["cut"]) for p in plans.values()] == [("large", 512, 4), ("ring", 0, 0),
+                                                                            ("large", 0, 2), ("large", 0, 4)]
     outs = {}
     for m in (9200, 4096, 2048, 1000):
         C = torch.full((m, 4092), np.nan, dtype=torch.float32, device="cuda")
@@ -158,16 +161,29 @@ def test_large_gemm_tile_variants_agree_bitwise():
     assert P.row_rel_err(outs[9200].cpu().numpy(), M.linear(a64, b64)) < 2e-6
 
 
-@pytest.mark.parametrize("M_,N,K", [
-    (256, 32, 64), (300, 4, 128), (257, 260, 192),      # ring tiles: edges, one to three K tiles
-    (1100, 4100, 64), (3000, 2052, 128),                # one round of cut 256 x 256 tiles, ragged
-    (4353, 4100, 64), (4353, 4100, 128), (4353, 4100, 192),   # a full round and a remainder of cut tiles
-    (6400, 4352, 192), (8449, 4100, 64), (12800, 5888, 128)])  # uncut remainder; two and four rounds
-def test_in_order_gemm_tile_and_round_edges_exact(M_, N, K):
+@pytest.mark.parametrize("M_,N,K,plan", [
+    # LDS ring, by tile: one K tile, fewer than its stages, more
+    (256, 32, 64, "ring 32x64"), (300, 4, 128, "ring 32x64"), (257, 260, 192, "ring 32x64"),
+    (352, 1028, 1024, "ring 32x64"), (1100, 4100, 64, "ring 64x64"), (900, 1028, 192, "ring 64x64"),
+    (260, 8196, 320, "ring 64x64"), (4353, 4100, 64, "ring 64x128"), (4353, 4100, 128, "ring 64x128"),
+    (4096, 4092, 320, "ring 64x128"),
+    # 256 x 256 tiles, less than a round of them: in four parts, two or whole (grids of no multiple of 8)
+    (1000, 4092, 64, "large 0 cut 4"), (1000, 4092, 128, "large 0 cut 4"), (1000, 4092, 192, "large 0 cut 4"),
+    (700, 4100, 1024, "large 0 cut 4"), (2048, 4092, 64, "large 0 cut 2"), (3000, 2052, 128, "large 0 cut 2"),
+    (520, 8196, 256, "large 0 cut 2"), (3000, 4100, 192, "large 0 cut 1"), (2000, 4100, 512, "large 0 cut 1"),
+    # rounds dealt evenly, then the rest in parts or whole, or no rest
+    (4353, 4100, 192, "large 256 cut 4"), (8192, 4100, 128, "large 512 cut 4"), (8449, 4100, 192, "large 512 cut 2"),
+    (12800, 5888, 128, "large 1024 cut 2"), (6400, 4352, 192, "large 256 cut 1"), (4096, 4092, 512, "large 256 cut 1"),
+    (4000, 8188, 256, "large 512 cut 1")])
+def test_in_order_gemm_tile_and_round_edges_exact(M_, N, K, plan):
     """Prefill-sized products on small integers, whose sums are exact in
     float32: every element equals the integer product, at the edges of the
-    tiles, with one, two and three K tiles, with one and several tiles per
-    workgroup and with the last round's tiles whole and cut."""
+    tiles, with one, two, three and more K tiles, with one and several tiles
+    per workgroup and with the last round's tiles whole and cut.  `plan` is
+    the kernel that the case is there for."""
+    p = E.op_gemm_plan(M_, N, K)
+    got = f"large {p['even']} cut {p['cut']}" if p["kernel"] == "large" else f"{p['kernel']} {p['rows']}x{p['cols']}"
+    assert got == plan
     g = torch.Generator().manual_seed(M_ + N + K)
     a = torch.randint(-3, 4, (M_, K), generator=g).float()
     b = torch.randint(-3, 4, (N, K), generator=g).float()
@@ -561,6 +577,38 @@ def test_small_bf16_prefill_and_decode_on_cu_shares_bitwise(small):
     finally:
         # the module's other tests read this policy's caches: leave them as
         # the whole-chip prefill wrote them
+        pol.prefill(ids, images=img_d, lang_ids=lang_d)
+        torch.cuda.synchronize()
+
+
+def test_small_bf16_prefill_on_sixty_cus_bitwise(small):
+    """Sixty CUs are no multiple of the eight XCDs: the large-M kernel then
+    deals its tiles round robin instead of in one range per XCD.  Hidden
+    states and cache rows equal the whole chip's."""
+    cfg, ids, img, lang, pol, tok, ref, _ = small
+    rows = len(ids) * cfg.prefix_len
+    plan = E.op_gemm_plan(rows, 2 * cfg.mlp, cfg.d, in_order=True, cus=60)
+    assert plan["kernel"] == "large" and plan["even"] > 0 and plan["workgroups"] == 60
+    img_d, lang_d = _dev(img), _dev(lang)
+    probe = [0, 31, 63]
+
+    def snap():
+        return [x for e in probe for x in (pol.read_state(E.STATE_H_LAST_PRE, e),
+                                           pol.read_state(E.STATE_K, e, cfg.layers - 1), pol.read_state(E.STATE_V, e, 0))]
+
+    base = snap()
+    mask = _quarter_mask(1)
+    mask[0] &= ~0xF
+    s = E.create_cu_masked_stream(0, mask)
+    try:
+        pol.bind_stream(s)
+        pol.prefill(ids, images=img_d, lang_ids=lang_d)
+        torch.cuda.ExternalStream(s).synchronize()
+        assert all(np.array_equal(x, y) for x, y in zip(base, snap()))
+    finally:
+        pol.bind_stream(torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        E.destroy_stream(s)
         pol.prefill(ids, images=img_d, lang_ids=lang_d)
         torch.cuda.synchronize()
 
