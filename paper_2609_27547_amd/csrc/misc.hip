@@ -214,7 +214,7 @@ void im2col(bool bf16, const float* img, int n, int cams, int H, int W, int P, v
 // lowest bin) and top-2 margin, one wave per row, and writes the token's
 // embedding as the next step's input row, all its loads issued together.
 // Latency bounds it (the weights come from HBM once a step): 32 rows of 4096
-// 20.0 -> 14.2 us and one row of 1024 9.4 -> 7.9 us against waves that walked all
+// 20.0 -> 13.0 us and one row of 1024 9.4 -> 7.9 us against waves that walked all
 // columns for four bins each and read the embedding 256 columns at a time.  An
 // element's summation order depends on d alone.
 EBRL_DEV float sum_xor32(float a, float b) {   // lanes < 32: a's pair sums, others: b's
@@ -374,16 +374,18 @@ __global__ __launch_bounds__(256, 2) void logits_kernel(LogitsArgs a)
 
 void action_logits(const LogitsArgs& a, hipStream_t s) {
     if (a.n <= 0) return;
-    // Rows per workgroup: one while the rows alone are few (each then has
-    // n_bins / 16 workgroups of its own), four from 16 rows on (a weight read
-    // serves four rows).  16-byte weight loads once a row gives all four waves
+    // Rows per workgroup: one up to 64 rows (each has n_bins / 16 workgroups of
+    // its own), four above (a weight read serves four rows); one against four, 256
+    // bins: d 4096, 24 rows 11.6 and 14.6 us, 32 13.0 and 15.5, 64 16.2 and 17.4, 80 19.9
+    // and 19.6, 128 26.1 and 20.6; d 1024, 32 rows 9.6 and 9.9, 64 11.7 and 11.5, 128 12.6
+    // and 11.6.  16-byte weight loads once a row gives all four waves
     // such a piece, 8-byte ones below; d alone decides, as it orders the sums.
     auto go = [&](auto kern, int rg) {
         hipLaunchKernelGGL(kern, dim3((a.n + rg - 1) / rg, (a.n_bins + LOGIT_BINS - 1) / LOGIT_BINS), dim3(256), 0, s,
                            a);
     };
     auto rows = [&](auto kern1, auto kern4) {
-        if (a.n <= 16) go(kern1, 1);
+        if (a.n <= 64) go(kern1, 1);
         else go(kern4, 4);
     };
     if (!a.bf16) rows(logits_kernel<float, 4, 1>, logits_kernel<float, 4, 4>);

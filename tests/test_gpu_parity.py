@@ -225,10 +225,10 @@ def test_fp32_gemm_long_k_rounds_exact(M_, N, K):
 
 
 @pytest.mark.parametrize("bf16", [True, False])
-@pytest.mark.parametrize("n_bins,d,n", [(10, 64, 3), (250, 192, 19)])
+@pytest.mark.parametrize("n_bins,d,n", [(10, 64, 3), (250, 192, 19), (250, 192, 64), (10, 64, 67)])
 def test_action_head_ragged_bins_rows_and_width(bf16, n_bins, d, n):
     """The action head where bins, rows and columns fill its waves partly
-    (one and four rows per workgroup), against the oracle."""
+    (up to 64 rows one per workgroup, above four), against the oracle."""
     cfg = M.Config("head", bf16=bf16, n_cams=0, img=0, patch=0, layers=1, d=d, q_heads=1, kv_heads=1, head_dim=64,
                    mlp=64, vocab=64, n_lang=5, n_bins=n_bins, n_action_tokens=4)
     pol = E.Policy(_ebrl_config(cfg, n, 5), seed=3)
@@ -250,7 +250,7 @@ def test_action_head_ragged_bins_rows_and_width(bf16, n_bins, d, n):
 
 
 @pytest.mark.parametrize("bf16", [True, False])
-@pytest.mark.parametrize("n_bins,d,n", [(70, 2112, 18), (16, 1088, 17)])
+@pytest.mark.parametrize("n_bins,d,n", [(70, 2112, 18), (16, 1088, 17), (70, 2112, 66), (16, 1088, 65)])
 def test_action_head_wide_rows_and_partial_row_groups(bf16, n_bins, d, n):
     """Widths around those where the head's waves load 16-byte instead of
     8-byte weight pieces (the last piece partly filled), bins past the last
