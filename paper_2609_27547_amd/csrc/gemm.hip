@@ -409,11 +409,16 @@ EBRL_DEV void tile_origin(int v, int tiles_m, int tiles_n, int bm, int bn, int& 
 // 64 rows.  Two LDS stages of 64 KB; a stage's four half-operands are refilled
 // as soon as both groups have read them, so up to 14 KB per wave are in flight
 // and no wait is for the loads just issued.
-//  * What bounds it: a CU's operand stream (64 KB per 8.4 MFLOP K tile; about
-//    72 GB/s per CU is what global_load_lds reaches from L2 here) and the
-//    sustained clock; 1.55 PFLOP/s at 8192 x 8192 x 8192 (fp32 output)
-//    against 1.33 for the 16-wave kernel that read, waited and multiplied in
-//    step, and 1.59 for hipBLASLt.
+//  * What bounds it: a K tile is 0.86 us of MFMAs at 2.4 GHz.  It takes 0.75 to
+//    0.9 us of a launch with few tiles and 1.24 to 1.39 us with one on every CU,
+//    where the clock falls to 2.1 GHz (0.98 us) and 256 CUs share the caches: each
+//    then streams 47-53 GB/s of operands, where a bare loop of such DMAs over
+//    panels in L2 reaches 130 and one over panels beyond it 27.  1.55 PFLOP/s at
+//    8192 x 8192 x 8192 (fp32 output) against 1.33 for the 16-wave kernel that read,
+//    waited and multiplied in step, and 1.59 for hipBLASLt.
+//  * Registers: 256 of 256.  The instances for plain stores, row remap and
+//    residual spill 9, 3 and 1 of them once a tile, outside the K loop; the gate/up
+//    and QKV ones none.
 //  * Workgroups are persistent (one per CU): the next tile's first DMAs are
 //    issued before the epilogue of the current one, whose stores then drain
 //    behind the next tile's first K tile (7B-class gate/up, 8329 x 22016 x
@@ -661,11 +666,13 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_big_kernel(
 
 // Small outputs (fewer 256 x 256 tiles than CUs): BM x BN tiles on four waves
 // (2 x 2), a ring of ST K tiles in LDS with ST - 1 of them in flight, one
-// barrier per K tile.  These launches are held by each CU's operand stream
-// (about 72 GB/s): the two-stage kernel it replaces waited a full memory
-// latency per K tile (0.6-0.9 us), here a 64 x 64 tile takes 0.27 us per K
-// tile.  424 x 1024 x 4096: 39 -> 15 us; 800 x 1024 x 4096: 39 -> 17 us; 424 x
-// 3072 x 1024: 9.9 -> 7.2 us.  Same K order as the kernel above.
+// barrier per K tile.  The two-stage kernel it replaces waited a full memory
+// latency per K tile (0.6-0.9 us); here a K tile takes 0.18 (32 x 64), 0.23 (64 x
+// 64) and 0.35 us (64 x 128) with one workgroup on a CU, 0.26, 0.36 and 0.61 with
+// two, i.e. 70 and 80-94 GB/s of operands per CU whatever the tile and the depth
+// of the ring; what holds it there is not isolated (a bare loop of such DMAs
+// from L2 reaches 130).  424 x 1024 x 4096: 39 -> 15 us; 800 x 1024 x 4096: 39 -> 17
+// us; 424 x 3072 x 1024: 9.9 -> 8.0 us.  Same K order as the kernel above.
 template <int BM, int BN, int ST, bool PAIRED, class Epi>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb, int M, int N, int K, Epi epi)
