@@ -664,7 +664,7 @@ def main():
     traffic = stored_traffic(args.workload) if dominant == E.K_GEMM else None
     roofline.update({"frac": round(achieved / roofline["peak"], 4),
                      "traffic": traffic["traffic_bytes_per_launch"] if traffic else None,
-                     "kernel": ({E.K_GEMM: "gemm_bf16_big_kernel (projections, M >= 256)",
+                     "kernel": ({E.K_GEMM: "gemm_bf16_big_kernel, gemm_bf16_ring_kernel (projections, M >= 256)",
                                  E.K_GEMM_SKINNY: "gemm_bf16_decode_kernel (decode projections, split-K reduced in-kernel)",
                                  E.K_ATTN_PREFILL: "attn_prefill_bf16_kernel",
                                  E.K_ATTN_DECODE: "attn_decode_bf16_kernel",

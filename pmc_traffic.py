@@ -64,8 +64,10 @@ def sources_hash(paths=GEMM_SOURCES) -> str:
 
 def _per_dispatch(d: str, counter: str, name_part: str):
     """Counter value (KiB) of every dispatch whose kernel name contains
-    name_part, from the rocprofv3 output under d (sqlite or csv)."""
+    name_part (or one of several, divided by |), from the rocprofv3 output
+    under d (sqlite or csv)."""
     vals = {}
+    parts = name_part.split("|")
     dbs = glob.glob(os.path.join(d, "**", "*results.db"), recursive=True)
     for db in dbs:
         import sqlite3
@@ -73,12 +75,12 @@ def _per_dispatch(d: str, counter: str, name_part: str):
         for pid, disp, name, value in cur.execute(
                 "select pid, dispatch_id, kernel_name, value from counters_collection where counter_name = ?",
                 (counter,)):
-            if name_part in name:
+            if any(p in name for p in parts):
                 vals[(db, pid, disp)] = float(value)
     for f in glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True):
         with open(f, newline="") as fh:
             for r in csv.DictReader(fh):
-                if r["Counter_Name"] == counter and name_part in r["Kernel_Name"]:
+                if r["Counter_Name"] == counter and any(p in r["Kernel_Name"] for p in parts):
                     vals[(f, r["Process_Id"], r["Dispatch_Id"])] = float(r["Counter_Value"])
     if not dbs and not vals:
         sys.exit(f"no rocprofv3 counter output under {d}")
@@ -130,8 +132,8 @@ def kstats_main(args):
     lines = [f"# {args.title}", "", "Command (repository root on the GPU host; `cd /tmp && export TMPDIR=/tmp` first):",
              "", "```", args.command, "```", "",
              f"Total kernel time {total / 1e6:.1f} ms over {len(rows)} dispatches.", ""]
-    fams = [("gemm_bf16_big_kernel (all epilogues: the bench's large-M GEMM class)",
-             lambda n: "gemm_bf16_big_kernel" in n),
+    fams = [("gemm_bf16_big_kernel, gemm_bf16_ring_kernel (all epilogues: the bench's large-M GEMM class)",
+             lambda n: "gemm_bf16_big_kernel" in n or "gemm_bf16_ring_kernel" in n),
             ("gemm_bf16_decode_kernel (all epilogues)", lambda n: "gemm_bf16_decode_kernel" in n),
             ("attn_prefill_bf16_kernel", lambda n: "attn_prefill_bf16_kernel" in n),
             ("attn_decode_bf16_kernel", lambda n: "attn_decode" in n)]
