@@ -18,8 +18,8 @@ extern "C" {
  * path, fp32 accumulate); EBRL_DTYPE_FP32: float32.  C is float32 row-major
  * with leading dimension N.  Requires M, N >= 1, K >= 8 and K % 8 == 0;
  * the kernel choice (tile, split over K) depends only on (M, N, K).
- * stream: hipStream_t or NULL.  K splits (bf16, M < 256) write their partial sums
- * to a workspace the library allocates on the first call per (device,
+ * stream: hipStream_t or NULL.  K splits (bf16, M < 256) write their partial
+ * sums to a workspace the library allocates on the first call per (device,
  * stream) and keeps until the process ends, so calls on different streams
  * may overlap.  Returns EBRL_E_OOM if that allocation fails. */
 int ebrl_op_gemm(int32_t dtype, const void* A, const void* B, float* C, int32_t M, int32_t N,
@@ -28,8 +28,8 @@ int ebrl_op_gemm(int32_t dtype, const void* A, const void* B, float* C, int32_t 
 /* The kernel that computes a product, for tests and timings that have to know
  * which one they reach; host arithmetic, no GPU needed.  in_order 0: as
  * ebrl_op_gemm; else as the prefill, ViT and expert projections, which sum K
- * in order at any M (with ebrl_op_gemm's output).  cus: compute units of the stream (ebrl_op_gemm: 256).
- * plan[0] 0: register-staged tiles (K not a multiple of 64), 1: 256 x 256
+ * in order at any M (with ebrl_op_gemm's output).  cus: compute units of the
+ * stream (ebrl_op_gemm: 256).  plan[0] 0: register-staged tiles (K not a multiple of 64), 1: 256 x 256
  * tiles, 2: LDS ring, 3: decode, 4: fp32; [1], [2] tile rows and columns; [3]
  * K splits; [4] workgroups; [5] K groups a decode wave keeps in LDS; [6], [7]
  * kernel 1: tiles dealt evenly, and the parts each tile of the last round is
@@ -46,8 +46,8 @@ int ebrl_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t in
  * each GPU the library runs on holds until the process ends; the call
  * allocates nothing and issues no memset.  Shapes whose split would write
  * more partial sums than the array holds return EBRL_E_INVALID (without a
- * split, i.e. M >= 256 or fp32, any shape is accepted).  Every call on one GPU shares
- * that GPU's array: calls that overlap in time on one GPU (on different
+ * split, i.e. M >= 256 or fp32, any shape is accepted).  Every call on one GPU
+ * shares that GPU's array: calls that overlap in time on one GPU (on different
  * streams or from different host threads) race and give wrong results;
  * calls ordered on one stream do not.  Same arguments and errors as
  * ebrl_op_gemm otherwise. */

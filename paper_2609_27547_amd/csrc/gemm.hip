@@ -1285,8 +1285,8 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ ws, int splits, i
 
 // ------------------------------------------------------------- dispatch --
 
-// Tile and split choice depend only on (M, N, K) and the stream's CU count;
-// the split count, the only one that orders sums, on (N, K) alone.
+// Tile and split choice depend only on (M, N, K), the stream's CU count and the
+// epilogue; the split count, the only one that orders sums, on (N, K) alone.
 struct GemmPlan {
     int bm; int splits; int k_per_split;
     bool seq;      // K in order: the large-M kernel (bm 256) or the ring kernel (bm x bn)
